@@ -348,7 +348,6 @@ pbvd_status launch_group(const CodeSet &cs, int ci, const TileGroup &g, const ui
         pbvd::WaveLaunchRequest req{};
         pbvd::wave::Args &a = req.args;
         a.syms = d_syms;
-        a.in_end = d_syms + sym_bytes;
         a.out = d_out;
         a.out_mode = pbvd::kOutBytes;
         a.sp = sp;
@@ -401,7 +400,6 @@ pbvd_status launch_fused(const CodeSet &cs, int K, const FusedGroup &g, const ui
     pbvd::WaveLaunchRequest req{};
     pbvd::wave::Args &a = req.args;
     a.syms = d_syms;
-    a.in_end = d_syms + sym_bytes;
     a.out = d_out;
     a.out_mode = pbvd::kOutBytes;
     a.sp = sp;

@@ -592,7 +592,7 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     if (pb_count == 0) return PBVD_OK;
     const int64_t slot = wave_slot_dwords(c);
     // single_launch (the debug survivor export): each wave also stores its
-    // per-stage decisions, after the path words of all waves
+    // per-stage decisions, after the tags of all waves
     const int64_t per_launch = launch_limit(p, ws, single_launch ? 2 * slot : slot);
     if (per_launch < 1)
         return fail(PBVD_EINVAL, "one PB's survivors (%lld bytes) do not fit the static scratch",
@@ -618,7 +618,6 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     pbvd::WaveLaunchRequest req{};
     pbvd::wave::Args &a = req.args;
     a.syms = (const uint8_t *)d_syms;
-    a.in_end = a.syms + T * c.R;
     a.out = d_out;
     a.out_words = direct ? nullptr : ws.words;
     a.out_bytes = out_bytes;
@@ -956,7 +955,7 @@ pbvd_status pbvd_debug_survivors(pbvd_plan *p, const void *d_syms, int64_t n_bit
     st = run_decode(p, p->ws, d_syms, n_bits, pb_first, pb_count, d_out_bits, nullptr, s, &g, true, &lb);
     if (st != PBVD_OK || pb_count == 0) return st;
     pbvd::SurvivorView v{};
-    // the state-parallel kernel's per-stage decisions follow its path words
+    // the state-parallel kernel's per-stage decisions follow its tags
     v.sp = lb == kWaveLb ? p->ws.sp + pb_count * wave_slot_dwords(p->code) : p->ws.sp;
     v.wave = lb == kWaveLb ? 1 : 0;
     v.sp_wave_dwords = lb == kWaveLb ? wave_slot_dwords(p->code) : slot_dwords(p->code, lb);

@@ -14,42 +14,52 @@
 // positions that differ in bit ph = t mod V: the even one holds the upper
 // predecessor S_2j, the odd one S_2j+1, and the new metrics of S_j (input 0)
 // and S_j+2^(V-1) (input 1) go back to the even and the odd position.
-// Position u is lane u mod 64, register slot u / 64 (K = 8: 2 slots, K = 9:
-// 4).  For K < 7 the lanes above 2^V repeat the low ones.
+// Bits 0..5 of a position choose the lane (see position_of_lane), the bits
+// above the register slot (K = 8: 2 slots, K = 9: 4).  For K < 7 the lanes
+// above 2^V repeat the low ones.
 //
-// Exchanges.  At phase ph every position needs the metric of the pair's
-// even and odd position: lane bits 0 and 1 with DPP quad permutes, bits 2
-// and 3 with DPP row shifts restricted to the banks that read across, bit 4
-// and 5 with the gfx950 permlane16/permlane32 swaps (one instruction gives
-// both halves), slot bits inside the lane.
+// A stage.  Each lane forms the two candidates that leave its position, the
+// one that stays (own target) and the one its partner takes, both as one
+// v_dot4_i32_i8 of the stage's R symbols (a scalar register, read from the
+// lane that loaded them) with the branch's code-word mask, accumulated onto
+// its metric; v_min_i32 then takes the partner's candidate through a DPP lane
+// swap.  The partner is lane ^ 1, 2, 7 or 8 for position bits 0..3: the swaps
+// DPP does in one instruction (quad permutes, half-row mirror, row rotation);
+// bits 4 and 5 use the gfx950 permlane16 / permlane32 swaps of the two
+// candidates, slot bits need no exchange.  That is 3 vector instructions per
+// stage (4 for bits 4 and 5) plus the symbol read.
 //
 // Branch metrics.  A branch's code word is c = (c^(1)..c^(R)) of Eq. 2; its
 // metric is sum over r of c_r q_r (the Sec. II distance minus a constant
-// shared by all branches of the stage, which changes no decision).  Each lane
-// keeps, per phase and slot, the code-word bits of its two branches as byte
-// masks and forms each metric with one v_dot4_i32_i8 of the stage's R
-// symbols (packed in one dword) and the mask.
+// shared by all branches of the stage, which changes no decision).  Metrics
+// are kept times 64 (mask bytes 0 / 64), the low six bits are the tag.
 //
-// Survivors.  dec = 1 when the lower branch (from S_2j+1) is strictly
-// cheaper, as Eq. 1 with ties to the upper branch.  The survivor memory is
-// kept by register exchange within a trip of W = V * floor(32 / V) stages (a
-// trip starts at phase 0): each position carries the decisions of the
-// survivor path into it, h = h_pred << 1 | dec, its predecessor's word
-// exchanged like the metric.  At the end of a trip the words go to HBM,
-// [trip][slot][lane]: the word at position u holds the W decisions of the
-// survivor into u over the trip, the k-th stage's at bit W-1-k.
+// Survivors.  The tag of a position carries the origin of its survivor path:
+// before the first stage of a round (position bits 0..5, phases 0..5) it is
+// set to the position itself, and the minimum carries it along, so after the
+// last phase of the round it is the position where the path was when the
+// round began.  Two candidates of equal metric differ first, from the top, in
+// the bit of the current phase (the bits above it have not been replaced
+// yet), which is 0 for the path from S_2j: the minimum keeps the upper
+// branch on ties, as Eq. 1 asks.  For K = 8, 9 the slot phases form a second
+// round, whose tag is the slot.  The tags of floor(32 / V) passes over all V
+// phases fill one dword, a trip of W = V * floor(32 / V) stages, which goes to
+// HBM as [trip][slot][position].
 //
-// Traceback (Alg. 1, Kernel 2), a trip at a time on the scalar unit.  A
-// state's input bit is bit t mod V of its position, and the predecessor's
-// position is the position with that bit replaced by the decision; after a
-// whole trip (a multiple of V stages) every bit has been replaced.  So from
-// the position P at a trip's end and its word h (v_readlane of lane P mod
-// 64), the position at the trip's start is the decisions of the trip's
-// first V stages, and the input bits of the trip are the decisions of its
-// stages V.. (for the first W-V stages) followed by the bits of P: two bit
-// reversals and shifts per trip instead of a step per stage.  A debug
-// variant also stores the per-stage decisions of every position, the
-// survivor layout of the plain method.
+// Traceback (Alg. 1, Kernel 2), V stages at a time on the scalar unit.  The
+// input bit of a stage is the bit of its phase in the position the path
+// reaches, and every bit is replaced once in V stages, so the V input bits of
+// a pass are the position P at its end, and the position at its start is the
+// tag stored for P.  A debug variant also stores the per-stage decisions of
+// every position, the survivor layout of the plain method.
+//
+// What bounds it: vector issue where several waves share a SIMD (K = 7: 26
+// instructions and a few waits for 6 stages), and for a lone wave the dependent
+// chain of every stage, dot product -> swap and minimum.  Path words exchanged
+// along with the metrics, a dot product after every exchange, and symbol loads
+// that each trip waited for (12.6 instructions per stage) took twice as long:
+// 2^20 bits of K = 7 in 2,048 blocks 47.1 -> 23.6 us per decode, 2^22 bits of
+// K = 8 rate 1/3 205 -> 104 us, 4096 bits of K = 3 18.6 -> 11.8 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -63,53 +73,33 @@
 namespace pbvd {
 namespace wave {
 
-// Even and odd position's value of the pair whose bit is lane bit B.
+// Position bits 0..5 of a lane: lane = u0 ^ 2 u1 ^ 7 u2 ^ 8 u3 ^ 16 u4 ^ 32 u5,
+// which is its own inverse.  Flipping position bit 2 is then lane ^ 7, the DPP
+// half-row mirror (no DPP control flips lane bit 2 alone).
+__device__ __forceinline__ int position_of_lane(int lane) { return lane ^ (lane & 4 ? 3 : 0); }
+
+// v of the lane whose position differs in bit B (B < 4).
 template <int B>
-__device__ __forceinline__ void pair_values(int v, int &e, int &o) {
-    if constexpr (B == 0) {
-        e = __builtin_amdgcn_mov_dpp(v, quad_sel(0, 0, 2, 2), 0xf, 0xf, false);
-        o = __builtin_amdgcn_mov_dpp(v, quad_sel(1, 1, 3, 3), 0xf, 0xf, false);
-    } else if constexpr (B == 1) {
-        e = __builtin_amdgcn_mov_dpp(v, quad_sel(0, 1, 0, 1), 0xf, 0xf, false);
-        o = __builtin_amdgcn_mov_dpp(v, quad_sel(2, 3, 2, 3), 0xf, 0xf, false);
-    } else if constexpr (B == 2) {
-        // banks (groups of 4 lanes) 1 and 3 read 4 lanes down, 0 and 2 up
-        e = __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xa, false);
-        o = __builtin_amdgcn_update_dpp(v, v, 0x104, 0xf, 0x5, false);
-    } else if constexpr (B == 3) {
-        e = __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xc, false);
-        o = __builtin_amdgcn_update_dpp(v, v, 0x108, 0xf, 0x3, false);
-    } else if constexpr (B == 4) {
-        // rows 1, 3 of the first operand swap with rows 0, 2 of the second:
-        // the first result holds rows (0, 0, 2, 2), the second (1, 1, 3, 3)
-        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
-        e = (int)r[0];
-        o = (int)r[1];
-    } else {
-        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
-        e = (int)r[0];
-        o = (int)r[1];
-    }
+__device__ __forceinline__ int swap_lane(int v) {
+    constexpr int kCtrl = B == 0 ? quad_sel(1, 0, 3, 2)    // lane ^ 1
+                        : B == 1 ? quad_sel(2, 3, 0, 1)    // lane ^ 2
+                        : B == 2 ? 0x141                   // row_half_mirror: lane ^ 7
+                                 : 0x128;                  // row_ror:8: lane ^ 8
+    return __builtin_amdgcn_mov_dpp(v, kCtrl, 0xf, 0xf, true);
 }
 
-// up += dot(q of lane LANE of the row, mu); lo += dot(q of lane LANE, ml):
-// v_dot4c_i32_i8 with the symbol dword broadcast by DPP row_newbcast (written
-// out: the compiler does not fold the broadcast into the dot product).  A
-// dot product's result may be read by another vector instruction only three
-// wait states after it is written, so the pair ends with s_nop 2 (the
-// compiler cannot see into the statement to insert them).
-template <int LANE>
-__device__ __forceinline__ void dot_pair(int &up, int &lo, uint32_t q, uint32_t mu, uint32_t ml) {
-    asm("v_dot4c_i32_i8_dpp %0, %2, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_dot4c_i32_i8_dpp %1, %2, %4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 2"
-        : "+v"(up), "+v"(lo)
-        : "v"(q), "v"(mu), "v"(ml), "n"(LANE));
+// pm plus the branch metric.  The clamp (metrics never reach it) keeps the
+// three-operand form of the dot product: without it the compiler takes the
+// accumulating form, which needs a copy of pm for every second candidate.
+__device__ __forceinline__ int branch(int q, uint32_t mask, int pm) {
+    return __builtin_amdgcn_sdot4(q, (int)mask, pm, true);
 }
 
-// acc << 1 | (diff's sign bit)
-__device__ __forceinline__ uint32_t push_sign(uint32_t acc, int diff) {
-    return __builtin_amdgcn_alignbit(acc, (uint32_t)diff, 31);
+// (acc:v) >> N of the 64-bit pair with v on top: the low N bits of v enter acc
+// at the top.
+template <int N>
+__device__ __forceinline__ uint32_t push_low(uint32_t acc, int v) {
+    return __builtin_amdgcn_alignbit((uint32_t)v, acc, N);
 }
 
 __device__ __forceinline__ int wave_min(int v) {
@@ -117,8 +107,6 @@ __device__ __forceinline__ int wave_min(int v) {
     for (int m = 1; m < kWave; m <<= 1) v = min(v, __shfl_xor(v, m, kWave));
     return v;
 }
-
-__device__ __forceinline__ int parity32(uint32_t x) { return __builtin_popcount(x) & 1; }
 
 // A 64-bit value every lane holds alike, made provably wave-uniform.
 __device__ __forceinline__ int64_t uniform64(int64_t v) {
@@ -128,9 +116,9 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 }
 
 template <int V>
-__device__ __forceinline__ uint32_t rotr_rt32(uint32_t u, int s) {
+__device__ __forceinline__ uint32_t rotl_rt32(uint32_t u, int s) {
     s %= V;
-    return s == 0 ? u : (((u >> s) | (u << (V - s))) & ((1u << V) - 1u));
+    return s == 0 ? u : (((u << s) | (u >> (V - s))) & ((1u << V) - 1u));
 }
 
 // The PB a wave decodes.
@@ -145,27 +133,8 @@ struct Job {
     int32_t *pm_out;     // final metrics or null
 };
 
-// New metric and path word of a position from its two candidates: the
-// lower (odd) branch wins only when strictly cheaper (Eq. 1, ties to the
-// upper branch); h = (the winner's word) << 1 | dec in one add with carry
-// (h + h + dec).  Written out because the compiler spends three
-// instructions on the word.  A VCC written by a vector instruction is read
-// as a mask two wait states later, and the words written here may be read
-// by DPP (two wait states) right after the statement.
-__device__ __forceinline__ void select_path(int &pm, uint32_t &h, int up, int lo, uint32_t he, uint32_t ho) {
-    asm("v_cmp_lt_i32 vcc, %[lo], %[up]\n\t"
-        "v_min_i32 %[pm], %[lo], %[up]\n\t"
-        "s_nop 0\n\t"
-        "v_cndmask_b32 %[h], %[he], %[ho], vcc\n\t"
-        "v_addc_co_u32 %[h], vcc, %[h], %[h], vcc\n\t"
-        "s_nop 1"
-        : [pm] "=&v"(pm), [h] "=&v"(h)
-        : [lo] "v"(lo), [up] "v"(up), [he] "v"(he), [ho] "v"(ho)
-        : "vcc");
-}
-
 // DEC: also store each stage's decisions (the debug survivor export) at
-// dec_wave, in the [trip][slot][lane] layout of the path words.
+// dec_wave, in the [trip][slot][position] layout of the tags.
 template <int V, bool DEC>
 __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const WaveCode &code, uint32_t *sp_wave,
                                           uint32_t *dec_wave) {
@@ -174,7 +143,8 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     constexpr int NL = N < kWave ? N : kWave;   // distinct positions per slot
     constexpr int LB = V < 6 ? V : 6;            // lane bits of a position
     constexpr int W = trip_stages(V);
-    constexpr int G = (W + 15) / 16;             // symbol dwords per lane and trip
+    constexpr int NP = W / V;                    // passes over the V phases per trip
+    constexpr int kTag = 63;                     // tag bits of a metric
 
     // the lane number through an empty asm statement: what derives from it
     // (the branch masks above all) is recomputed for each PB instead of
@@ -192,135 +162,146 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
 
     // Symbols: the R symbols of stage t are packed in one dword (bytes
     // 0..R-1; the bytes above belong to the next stage and meet zero mask
-    // bytes).  Lane l holds those of the trip's stage g*16 + (l mod 16) in
-    // qv[g] (every row of 16 lanes the same), and each stage broadcasts its
-    // dword from lane k mod 16 of every row into the dot product (DPP
-    // row_newbcast).  A trip's symbols are loaded a trip ahead.
-    const uint8_t *const in = j.in;
-    const int sl = lane & 15;
-    auto load_q = [&](uint32_t (&lo)[G], uint32_t (&hi)[G], uint32_t (&mis)[G], int tt0) PBVD_INLINE_LAMBDA {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            int t = tt0 + g * 16 + sl;
-            t = t < 0 ? 0 : t;  // stages before the first are never used
-            const uint8_t *p = in + (int64_t)t * R;  // R: the code's rate, wave-uniform
-            mis[g] = (uint32_t)((uintptr_t)p & 3u);
-            const uint8_t *pa = p - mis[g];
-            if (pa + 8 <= a.in_end) {
-                const uint32_t *w = reinterpret_cast<const uint32_t *>(pa);
-                lo[g] = __builtin_nontemporal_load(w);
-                hi[g] = __builtin_nontemporal_load(w + 1);
-            } else {
-                // the end of the input (bytes past it read as 0)
-                uint32_t v0 = 0u, v1 = 0u;
-#pragma unroll
-                for (int bb = 0; bb < 4; ++bb) {
-                    if (pa + bb < a.in_end) v0 |= (uint32_t)pa[bb] << (8 * bb);
-                    if (pa + 4 + bb < a.in_end) v1 |= (uint32_t)pa[4 + bb] << (8 * bb);
-                }
-                lo[g] = v0;
-                hi[g] = v1;
-            }
-        }
+    // bytes).  Lane l holds those of stage l of two trips (2 W <= 64 stages),
+    // and each stage reads its dword into a scalar register; the two trips'
+    // loads are issued two trips ahead.  They come through a buffer resource
+    // that holds the dwords of the PB's own symbols: loads past it return 0
+    // without a branch, so they stay in flight until they are used (a branch
+    // around the end of the input made every trip wait for its loads).
+    static_assert(2 * W <= kWave, "a lane per stage of two trips");
+    const uint32_t mis0 = (uint32_t)((uintptr_t)j.in & 3u);
+    const uint8_t *const in_dw = j.in - mis0;
+    const __amdgpu_buffer_rsrc_t in_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t *>(in_dw), (short)0, (int)(mis0 + (uint32_t)(len * R) + 3u) & ~3, kBufferFlags);
+    struct Raw {
+        uint32_t lo, hi, at;  // two dwords and the byte offset of the first symbol in them (mod 4)
     };
-    auto make_q = [&](const uint32_t (&lo)[G], const uint32_t (&hi)[G], const uint32_t (&mis)[G],
-                      uint32_t (&qv)[G]) PBVD_INLINE_LAMBDA {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            uint32_t q = __builtin_amdgcn_alignbyte(hi[g], lo[g], mis[g]);
-            if (hard) q = 0x01010101u + (q & 0x01010101u) * 0xfeu;  // bit -> +1 / -1
-            qv[g] = q;
-        }
-        // two wait states between these writes and the DPP reads of qv
-        if constexpr (G == 1) asm volatile("s_nop 1" : "+v"(qv[0]));
-        else asm volatile("s_nop 1" : "+v"(qv[0]), "+v"(qv[1]));
+    auto load_q = [&](int tt0) PBVD_INLINE_LAMBDA {
+        int t = tt0 + lane;
+        t = t < 0 ? 0 : t;  // stages before the first are never used
+        Raw r;
+        r.at = (uint32_t)(t * R) + mis0;  // R: the code's rate, wave-uniform
+        // dword by dword: each is in bounds or not as a whole
+        r.lo = __builtin_amdgcn_raw_buffer_load_b32(in_rsrc, r.at & ~3u, 0, kRowPolicy);
+        r.hi = __builtin_amdgcn_raw_buffer_load_b32(in_rsrc, (r.at & ~3u) + 4, 0, kRowPolicy);
+        return r;
+    };
+    auto make_q = [&](const Raw &r) PBVD_INLINE_LAMBDA {
+        const uint32_t q = __builtin_amdgcn_alignbyte(r.hi, r.lo, r.at);
+        return hard ? 0x01010101u + (q & 0x01010101u) * 0xfeu : q;  // bit -> +1 / -1
     };
 
-    // the first trip's symbols are requested before the masks are formed
-    // (with one slot: with more, the masks' registers leave no room)
-    uint32_t nlo[G], nhi[G], nmis[G];
-    if constexpr (SL == 1) load_q(nlo, nhi, nmis, -off);
+    // the first trip's and the next two trips' symbols are requested before
+    // the masks are formed
+    const Raw raw_first = load_q(-off);
+    Raw raw_next = load_q(W - off);
 
-    // ---- per-lane code-word masks of the two branches into each position,
-    //      per phase and slot (Eq. 2 with the run-time generators) ----
-    uint32_t mup[V][SL], mlo[V][SL];
+    // ---- code-word masks (bytes 0 / 64) of the two branches that leave each
+    //      position, per phase and slot (Eq. 2 with the run-time generators):
+    //      m0 / m1 the one that stays and the one the partner takes (lane
+    //      swaps), or the ones with input 0 and 1 (permlane and slot phases).
+    //      The register's state part enters as the parity of u and the
+    //      generator rotated like the state; the input adds g_{K-1}. ----
+    const int upos = position_of_lane(lane);
+    uint32_t gk = 0;  // 64 in the bytes of generators that tap the input
+#pragma unroll
+    for (int r = 0; r < 4; ++r) gk |= ((code.gen[r] >> V) & 1u) << (8 * r + 6);
+    uint32_t m0[V][SL], m1[V][SL];
 #pragma unroll
     for (int ph = 0; ph < V; ++ph) {
+        uint32_t rg[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rg[r] = rotl_rt32<V>(code.gen[r] & (uint32_t)(N - 1), ph);
 #pragma unroll
         for (int s = 0; s < SL; ++s) {
-            const uint32_t u = (uint32_t)(s * kWave + (lane & (NL - 1)));
-            const uint32_t even = u & ~(1u << ph);
-            const uint32_t se = rotr_rt32<V>(even, ph);   // the upper predecessor S_2j
-            const uint32_t x = (u >> ph) & 1u;             // input bit of the branch
-            const uint32_t reg = (x << V) | se;
-            uint32_t mu = 0, ml = 0;
+            const uint32_t u = (uint32_t)(s * kWave + (upos & (NL - 1)));
+            uint32_t c = 0;  // bit counts (at most 8) in bytes; generators past R are 0
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {  // generators past R are 0: zero mask bytes
-                mu |= (uint32_t)parity32(code.gen[r] & reg) << (8 * r);
-                ml |= (uint32_t)parity32(code.gen[r] & (reg | 1u)) << (8 * r);
-            }
-            mup[ph][s] = mu;
-            mlo[ph][s] = ml;
+            for (int r = 0; r < 4; ++r) c |= (uint32_t)__builtin_popcount(u & rg[r]) << (8 * r);
+            c = (c & 0x01010101u) << 6;
+            if (ph < 4 && ph < LB && ((u >> ph) & 1u)) c ^= gk;  // the branch that stays has input u_ph
+            m0[ph][s] = c;
+            m1[ph][s] = c ^ gk;
         }
     }
 
-    if constexpr (SL > 1) load_q(nlo, nhi, nmis, -off);
-
     // ---- initial metrics: with a known start, state 0 (position 0 at any
-    //      phase) at 0 and the others at 8192; otherwise all 0 ----
+    //      phase) at 0 and the others at 8192; otherwise all 0; tags set for
+    //      the first round ----
     int pm[SL];
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
-        const int u = s * kWave + (lane & (NL - 1));
-        pm[s] = (j.known && u != 0) ? 8192 : 0;
+        const int u = s * kWave + (upos & (NL - 1));
+        pm[s] = ((j.known && u != 0) ? 8192 * (kTag + 1) : 0) | (upos & (NL - 1));
     }
 
-    // path words (register exchange within a trip)
+    // tags of the trip's passes, the last pushed on top
     uint32_t hist[SL];
 #pragma unroll
     for (int s = 0; s < SL; ++s) hist[s] = 0;
 
-    uint32_t *const sp_lane = sp_wave + lane;  // [trip][slot][lane]
+    uint32_t *const sp_lane = sp_wave + lane;  // [trip][slot][position]
+    uint32_t *const sp_pos = sp_wave + upos;
 
-    // one trellis stage, the k-th of its trip (phase k mod V); each
-    // candidate is its predecessor's metric plus the branch metric, the dot
-    // product accumulating onto the exchanged metric; the path words follow
-    // the metrics
-    auto stage = [&](auto kc, const uint32_t (&qv)[G], uint32_t (&acc)[SL]) PBVD_INLINE_LAMBDA {
+    // one trellis stage, the k-th of its trip (phase k mod V; symbols in lane
+    // H W + k of qv), and the tags at the end of a round.  live: the stage
+    // belongs to the PB (the first trip may start in the middle; its skipped
+    // rounds only set tags).
+    auto stage = [&](auto kc, auto hc, uint32_t qv, uint32_t (&acc)[SL], bool live) PBVD_INLINE_LAMBDA {
         constexpr int k = decltype(kc)::value;
         constexpr int PH = k % V;
-        const uint32_t q = qv[k / 16];
-        if constexpr (PH < LB) {
+        if (live) {
+            const int q = __builtin_amdgcn_readlane((int)qv, decltype(hc)::value * W + k);
+            if constexpr (PH < LB) {
 #pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                int up, lo, he, ho;
-                pair_values<PH>(pm[s], up, lo);
-                pair_values<PH>((int)hist[s], he, ho);
-                dot_pair<k % 16>(up, lo, q, mup[PH][s], mlo[PH][s]);
-                if constexpr (DEC) acc[s] = push_sign(acc[s], lo - up);
-                select_path(pm[s], hist[s], up, lo, (uint32_t)he, (uint32_t)ho);
-            }
-        } else {
-            constexpr int M = 1 << (PH - 6);  // slot bit
-#pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                if (s & M) continue;
-                int up0 = pm[s], lo0 = pm[s | M], up1 = pm[s], lo1 = pm[s | M];
-                const uint32_t he = hist[s], ho = hist[s | M];
-                dot_pair<k % 16>(up0, lo0, q, mup[PH][s], mlo[PH][s]);
-                dot_pair<k % 16>(up1, lo1, q, mup[PH][s | M], mlo[PH][s | M]);
-                if constexpr (DEC) {
-                    acc[s] = push_sign(acc[s], lo0 - up0);
-                    acc[s | M] = push_sign(acc[s | M], lo1 - up1);
+                for (int s = 0; s < SL; ++s) {
+                    const int a = branch(q, m0[PH][s], pm[s]);
+                    const int b = branch(q, m1[PH][s], pm[s]);
+                    if constexpr (PH < 4) {
+                        pm[s] = min(a, swap_lane<PH>(b));
+                    } else if constexpr (PH == 4) {
+                        // rows 1, 3 of the first operand swap with rows 0, 2
+                        // of the second: each lane gets the two candidates of
+                        // its own target (input 0 for rows 0, 2)
+                        const auto r = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false);
+                        pm[s] = min((int)r[0], (int)r[1]);
+                    } else {
+                        const auto r = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+                        pm[s] = min((int)r[0], (int)r[1]);
+                    }
                 }
-                select_path(pm[s], hist[s], up0, lo0, he, ho);
-                select_path(pm[s | M], hist[s | M], up1, lo1, he, ho);
+            } else {
+                constexpr int M = 1 << (PH - 6);  // slot bit
+#pragma unroll
+                for (int s = 0; s < SL; ++s) {
+                    if (s & M) continue;
+                    const int e = pm[s], o = pm[s | M];
+                    pm[s] = min(branch(q, m0[PH][s], e),
+                                branch(q, m0[PH][s | M], o));
+                    pm[s | M] = min(branch(q, m1[PH][s], e),
+                                    branch(q, m1[PH][s | M], o));
+                }
+            }
+            if constexpr (DEC) {
+                // the decision of this stage is its phase's bit of the tag
+                constexpr int bit = PH < 6 ? PH : PH - 6;
+#pragma unroll
+                for (int s = 0; s < SL; ++s) acc[s] = (acc[s] << 1) | (((uint32_t)pm[s] >> bit) & 1u);
+            }
+        }
+        if constexpr (PH == LB - 1 || PH == V - 1) {
+            constexpr int kBits = PH < 6 ? LB : V - 6;  // of the round that ends
+            constexpr bool kSlotsNext = PH < V - 1;
+#pragma unroll
+            for (int s = 0; s < SL; ++s) {
+                hist[s] = push_low<kBits>(hist[s], pm[s]);
+                pm[s] = (pm[s] & ~kTag) | (kSlotsNext ? s : (upos & (NL - 1)));
             }
         }
     };
 
-    // The traceback reads the path words of trips trip_bot..n_trips-1
-    // through a ring of kRing trips.  With one slot, the words of the last
+    // The traceback reads the tags of trips trip_bot..n_trips-1
+    // through a ring of kRing trips.  With one slot, the tags of the last
     // trip stay in registers and the loads of the trips below it are issued
     // at the start of the last forward trip, so that they have arrived when
     // the traceback starts.
@@ -335,8 +316,7 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     };
 
     // ---- forward procedure (Eq. 1) ----
-    for (int trip = 0; trip < n_trips; ++trip) {
-        const int tt0 = trip * W - off;  // stage of the trip's step 0
+    auto run_forward = [&](auto first, auto half, uint32_t qv, int trip) PBVD_INLINE_LAMBDA {
         if constexpr (kEarlyRing) {
             if (trip + 1 == n_trips) {
                 // trips below the last one are stored already (a clamped
@@ -347,36 +327,36 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
                 });
             }
         }
-        uint32_t qv[G];
-        make_q(nlo, nhi, nmis, qv);
-        if (trip + 1 < n_trips) load_q(nlo, nhi, nmis, tt0 + W);  // a trip ahead
         uint32_t acc[SL];
 #pragma unroll
         for (int s = 0; s < SL; ++s) acc[s] = 0;
-        if (trip > 0 || off == 0) {
-            static_for<0, W>([&](auto kc) PBVD_INLINE_LAMBDA {
-                stage(kc, qv, acc);
-                return true;
-            });
-        } else {
-            // the first trip starts at step off (its lower bits stay 0)
-            static_for<0, W>([&](auto kc) PBVD_INLINE_LAMBDA {
-                if (decltype(kc)::value >= off) stage(kc, qv, acc);
-                return true;
-            });
-        }
-        // step k of the trip at bit W-1-k
+        static_for<0, W>([&](auto kc) PBVD_INLINE_LAMBDA {
+            stage(kc, half, qv, acc, !decltype(first)::value || decltype(kc)::value >= off);
+            return true;
+        });
+        // pass p of the trip at bits 32 - V (NP - p) ..
 #pragma unroll
-        for (int s = 0; s < SL; ++s) __builtin_nontemporal_store(hist[s], sp_lane + (trip * SL + s) * kWave);
+        for (int s = 0; s < SL; ++s) __builtin_nontemporal_store(hist[s], sp_pos + (trip * SL + s) * kWave);
         if constexpr (DEC) {
+            // step k of the trip at bit W-1-k
 #pragma unroll
             for (int s = 0; s < SL; ++s)
-                __builtin_nontemporal_store(acc[s], dec_wave + lane + (trip * SL + s) * kWave);
+                __builtin_nontemporal_store(acc[s], dec_wave + upos + (trip * SL + s) * kWave);
         }
         // exact renormalization: every metric minus one shared value
-        const int ref = __builtin_amdgcn_readfirstlane(pm[0]);
+        const int ref = __builtin_amdgcn_readfirstlane(pm[0]) & ~kTag;
 #pragma unroll
         for (int s = 0; s < SL; ++s) pm[s] -= ref;
+    };
+    constexpr std::integral_constant<int, 0> kLow{};   // half of the lanes that hold a trip's symbols
+    constexpr std::integral_constant<int, 1> kHigh{};
+    run_forward(std::true_type{}, kLow, make_q(raw_first), 0);  // the first trip starts at step off
+    for (int trip = 1; trip < n_trips; trip += 2) {
+        const uint32_t qv = make_q(raw_next);
+        raw_next = load_q((trip + 2) * W - off);  // (past the input's end: 0)
+        run_forward(std::false_type{}, kLow, qv, trip);
+        if (trip + 1 == n_trips) break;
+        run_forward(std::false_type{}, kHigh, qv, trip + 1);
     }
 
     // ---- final metrics and traceback start (Sec. III-A; Sec. II at the end
@@ -384,6 +364,8 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     //      position u holds state u. ----
     uint32_t P = 0;
     if (j.argmin || j.pm_out) {
+#pragma unroll
+        for (int s = 0; s < SL; ++s) pm[s] >>= 6;  // drop the tags
         int m = pm[0];
 #pragma unroll
         for (int s = 1; s < SL; ++s) m = min(m, pm[s]);
@@ -392,22 +374,22 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
             int best = N;
 #pragma unroll
             for (int s = 0; s < SL; ++s) {
-                const int u = s * kWave + (lane & (NL - 1));
+                const int u = s * kWave + (upos & (NL - 1));
                 if (pm[s] == m && u < best) best = u;
             }
             P = (uint32_t)__builtin_amdgcn_readfirstlane(wave_min(best));
         }
-        if (j.pm_out && lane < NL) {
+        if (j.pm_out && upos < NL) {
 #pragma unroll
-            for (int s = 0; s < SL; ++s) j.pm_out[s * kWave + lane] = pm[s] - m;
+            for (int s = 0; s < SL; ++s) j.pm_out[s * kWave + upos] = pm[s] - m;
         }
     }
 
     // ---- traceback (Alg. 1, Kernel 2) ----
-    // A trip at a time from its path word (the last trip is full; stages
-    // below the decoded range at the bottom are harmless); the input bits of
-    // a trip form `word` (bit i = the trip's i-th stage) and the decoded
-    // ones are merged into the output word under assembly.
+    // A trip at a time from its tags (the last trip is full; stages below
+    // the decoded range at the bottom are harmless); the input bits of a trip
+    // form `word` (bit i = the trip's i-th stage) and the decoded ones are
+    // merged into the output word under assembly.
     const int store0 = j.store0, dec_end = j.dec_end;
     const int n_dec = dec_end - store0;
     int cm = (n_dec - 1) >> 5;  // output word under assembly (relative to the PB)
@@ -438,26 +420,34 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     };
 
     auto run_trip = [&](const uint32_t (&hw)[SL], int trip) PBVD_INLINE_LAMBDA {
-        uint32_t h;
-        if constexpr (SL == 1) {
-            h = (uint32_t)__builtin_amdgcn_readlane((int)hw[0], (int)(P & 63u));
-        } else {
+        uint32_t word = 0;
+        static_for<0, NP>([&](auto pc) PBVD_INLINE_LAMBDA {
+            constexpr int p = NP - 1 - decltype(pc)::value;
+            constexpr int sh = 32 - V * (NP - p);  // the pass's tags in the trip's word
+            word |= P << (V * p);
             const int l = (int)(P & 63u);
-            const uint32_t slot = P >> 6;
-            h = 0;
+            if constexpr (SL == 1) {
+                P = ((uint32_t)__builtin_amdgcn_readlane((int)hw[0], l) >> sh) & (uint32_t)(N - 1);
+            } else {
+                // the slot round's tag (top V - 6 bits of the pass) names the
+                // slot whose lane round led here
+                uint32_t f[SL];
 #pragma unroll
-            for (int s = 0; s < SL; ++s) {
-                const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)hw[s], l);
-                h = slot == (uint32_t)s ? v : h;
+                for (int s = 0; s < SL; ++s)
+                    f[s] = ((uint32_t)__builtin_amdgcn_readlane((int)hw[s], l) >> sh) & (uint32_t)(N - 1);
+                auto of_slot = [&](uint32_t slot) PBVD_INLINE_LAMBDA {
+                    uint32_t v = f[0];
+#pragma unroll
+                    for (int s = 1; s < SL; ++s) v = slot == (uint32_t)s ? f[s] : v;
+                    return v;
+                };
+                const uint32_t slot = of_slot(P >> 6) >> 6;
+                P = slot << 6 | (of_slot(slot) & 63u);
             }
-        }
-        // decision of the trip's stage k: bit W-1-k of h, i.e. bit
-        // 32-W+k of its reversal
-        const uint32_t rev = __builtin_bitreverse32(h);
-        const uint32_t word = (rev >> (32 - W + V)) | (P << (W - V));
-        P = (rev >> (32 - W)) & (uint32_t)(N - 1);
-        // decoded stages of the trip: [lo, hi), at bits lo - tt0 .. of word
+            return true;
+        });
         const int tt0 = trip * W - off;
+        // decoded stages of the trip: [lo, hi), at bits lo - tt0 .. of word
         const int lo = store0 > tt0 ? store0 : tt0;
         const int hi = dec_end < tt0 + W ? dec_end : tt0 + W;
         if (lo < hi) {
@@ -483,7 +473,9 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     const int trip_top = n_trips - 1;
     if constexpr (kEarlyRing) {
 #pragma unroll
-        for (int s = 0; s < SL; ++s) ring[0][s] = hist[s];
+        for (int s = 0; s < SL; ++s)  // from lane to position order (lane ^ 3 where lane bit 2 is set)
+            ring[0][s] = (uint32_t)__builtin_amdgcn_update_dpp((int)hist[s], (int)hist[s], quad_sel(3, 2, 1, 0), 0xf,
+                                                               0xa, false);
     } else {
         static_for<0, kRing - 1>([&](auto dc) PBVD_INLINE_LAMBDA {
             load_trip(ring[decltype(dc)::value], trip_top - decltype(dc)::value);

@@ -36,7 +36,6 @@ constexpr int kDescCodeShift = 8;
 
 struct Args {
     const uint8_t *syms;     // symbols; stream mode: stage 0 of the stream
-    const uint8_t *in_end;   // end of the readable symbol bytes
     uint8_t *out;            // packed decoded bits
     uint32_t *out_words;     // zeroed word staging (atomic output) or null
     int64_t out_bytes;       // bytes of `out` (direct output bound)
@@ -57,7 +56,7 @@ struct Args {
     uint32_t *counter;
     int64_t n_items;
     // debug mode (kModeDecisions): every stage's decisions, sp_wave_dwords
-    // per wave, the same [trip][slot][lane] layout as sp
+    // per wave, the same [trip][slot][position] layout as sp
     uint32_t *dec_sp;
     WaveCode codes[kMaxWaveCodes];  // stream mode: codes[0]
 };
