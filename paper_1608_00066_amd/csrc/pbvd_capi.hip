@@ -620,7 +620,6 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     a.syms = (const uint8_t *)d_syms;
     a.out = d_out;
     a.out_words = direct ? nullptr : ws.words;
-    a.out_bytes = out_bytes;
     a.final_pm = d_final_pm;
     a.sp = ws.sp;
     a.sp_wave_dwords = slot;

@@ -58,8 +58,8 @@
 // chain of every stage, dot product -> swap and minimum.  Path words exchanged
 // along with the metrics, a dot product after every exchange, and symbol loads
 // that each trip waited for (12.6 instructions per stage) took twice as long:
-// 2^20 bits of K = 7 in 2,048 blocks 47.1 -> 23.6 us per decode, 2^22 bits of
-// K = 8 rate 1/3 205 -> 104 us, 4096 bits of K = 3 18.6 -> 11.8 us.
+// 2^20 bits of K = 7 in 2,048 blocks 47.1 -> 21.4 us per decode, 2^22 bits of
+// K = 8 rate 1/3 205 -> 102 us, 4096 bits of K = 3 18.6 -> 10.9 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -240,8 +240,10 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
 #pragma unroll
     for (int s = 0; s < SL; ++s) hist[s] = 0;
 
-    uint32_t *const sp_lane = sp_wave + lane;  // [trip][slot][position]
-    uint32_t *const sp_pos = sp_wave + upos;
+    // [trip][slot][position] tags, through a buffer resource: the trip's
+    // offset is a scalar
+    const __amdgpu_buffer_rsrc_t sp_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        sp_wave, (short)0, (int)(pb_dwords(V, len) * 4), kBufferFlags);
 
     // one trellis stage, the k-th of its trip (phase k mod V; symbols in lane
     // H W + k of qv), and the tags at the end of a round.  live: the stage
@@ -312,7 +314,8 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     auto load_trip = [&](uint32_t (&dst)[SL], int trip) PBVD_INLINE_LAMBDA {
         trip = trip < trip_bot ? trip_bot : trip;
 #pragma unroll
-        for (int s = 0; s < SL; ++s) dst[s] = __builtin_nontemporal_load(sp_lane + (trip * SL + s) * kWave);
+        for (int s = 0; s < SL; ++s)
+            dst[s] = __builtin_amdgcn_raw_buffer_load_b32(sp_rsrc, lane * 4, (trip * SL + s) * (kWave * 4), kRowPolicy);
     };
 
     // ---- forward procedure (Eq. 1) ----
@@ -336,7 +339,8 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
         });
         // pass p of the trip at bits 32 - V (NP - p) ..
 #pragma unroll
-        for (int s = 0; s < SL; ++s) __builtin_nontemporal_store(hist[s], sp_pos + (trip * SL + s) * kWave);
+        for (int s = 0; s < SL; ++s)
+            __builtin_amdgcn_raw_buffer_store_b32(hist[s], sp_rsrc, upos * 4, (trip * SL + s) * (kWave * 4), kRowPolicy);
         if constexpr (DEC) {
             // step k of the trip at bit W-1-k
 #pragma unroll
@@ -386,36 +390,46 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     }
 
     // ---- traceback (Alg. 1, Kernel 2) ----
-    // A trip at a time from its tags (the last trip is full; stages below
-    // the decoded range at the bottom are harmless); the input bits of a trip
-    // form `word` (bit i = the trip's i-th stage) and the decoded ones are
-    // merged into the output word under assembly.
-    const int store0 = j.store0, dec_end = j.dec_end;
-    const int n_dec = dec_end - store0;
-    int cm = (n_dec - 1) >> 5;  // output word under assembly (relative to the PB)
-    uint32_t cw = 0;
-
-    auto flush = [&]() PBVD_INLINE_LAMBDA {
-        if (lane != 0) return;
-        const int rel = cm * 32;
-        const int m = n_dec - rel < 32 ? n_dec - rel : 32;
-        const int64_t bitpos = j.out_bit0 + rel;
-        if (a.out_mode == kOutDirect) {
-            const int64_t byte = bitpos >> 3;
-            if (m == 32 && byte + 4 <= a.out_bytes) {
-                *reinterpret_cast<uint32_t *>(a.out + byte) = cw;
-            } else {
-                for (int bb = 0; bb < ((m + 7) >> 3); ++bb)
-                    if (byte + bb < a.out_bytes) a.out[byte + bb] = (uint8_t)(cw >> (8 * bb));
-            }
-        } else if (a.out_mode == kOutAtomic) {
+    // A trip at a time from its tags; stages below the decoded range at the
+    // bottom are harmless.  Only the chain of positions runs trip by trip;
+    // the input bits of a trip (bit i = its i-th stage) go to a lane of
+    // `bits`, trip base + l to lane l.  Once kChunk trips are there (or the
+    // last), every lane makes one output word from the two or three trips
+    // it spans and all words are stored at once.  (Merging and storing word
+    // by word inside the chain took twice as long: 13.8 k -> 7.6 k cycles
+    // for the 20 trips of a K = 7 block of 512 bits.)
+    const int n_dec = j.dec_end - j.store0;
+    constexpr int kChunk = kWave - 2;  // lanes 62, 63: the two trips above the chunk
+    int base = trip_bot + (n_trips - 1 - trip_bot) / kChunk * kChunk;
+    uint32_t bits = 0;
+    auto emit = [&]() PBVD_INLINE_LAMBDA {
+        // word m of the PB starts at virtual stage first + 32 m; this
+        // chunk's words start in trips base .. base + kChunk - 1
+        const int first = j.store0 + off;
+        const int lowest = base * W - first;
+        const int m = (lowest > 0 ? (lowest + 31) >> 5 : 0) + lane;
+        const int at = 32 * m - lowest;  // from the chunk's first stage
+        const int i = at / W, sh = at - i * W;
+        uint32_t v = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i, (int)bits) >> sh;
+        v |= (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i + 4, (int)bits) << 1 << (W - 1 - sh);
+        const uint32_t top = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i + 8, (int)bits);
+        if (2 * W - sh < 32) v |= top << (2 * W - sh);
+        const int nb = n_dec - 32 * m < 32 ? n_dec - 32 * m : 32;
+        if (i >= kChunk || nb <= 0) return;
+        if (nb < 32) v &= (1u << nb) - 1u;
+        const int64_t bitpos = j.out_bit0 + 32 * m;
+        if (a.out_mode == kOutAtomic) {
             const uint32_t shf = (uint32_t)(bitpos & 31);
             uint32_t *wp = a.out_words + (bitpos >> 5);
-            atomicOr(wp, cw << shf);
-            if (shf && (cw >> (32 - shf))) atomicOr(wp + 1, cw >> (32 - shf));
+            atomicOr(wp, v << shf);
+            if (shf && (v >> (32 - shf))) atomicOr(wp + 1, v >> (32 - shf));
+            return;
+        }
+        uint8_t *ob = a.out + (bitpos >> 3);
+        if (nb == 32 && ((uintptr_t)ob & 3u) == 0) {
+            *reinterpret_cast<uint32_t *>(ob) = v;
         } else {
-            uint8_t *ob = a.out + (bitpos >> 3);
-            for (int bb = 0; bb < ((m + 7) >> 3); ++bb) ob[bb] = (uint8_t)(cw >> (8 * bb));
+            for (int bb = 0; bb < ((nb + 7) >> 3); ++bb) ob[bb] = (uint8_t)(v >> (8 * bb));
         }
     };
 
@@ -446,27 +460,14 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
             }
             return true;
         });
-        const int tt0 = trip * W - off;
-        // decoded stages of the trip: [lo, hi), at bits lo - tt0 .. of word
-        const int lo = store0 > tt0 ? store0 : tt0;
-        const int hi = dec_end < tt0 + W ? dec_end : tt0 + W;
-        if (lo < hi) {
-            const int nb = hi - lo;
-            uint32_t bits = word >> (lo - tt0);
-            bits = nb >= 32 ? bits : bits & ((1u << nb) - 1u);
-            const int r = lo - store0;   // first decoded bit, relative
-            const int base = cm * 32;
-            if (r >= base) {
-                cw |= bits << (r - base);
-            } else {
-                // the chunk reaches into the word below: the current one is
-                // complete (r < base <= r + nb <= base + 32)
-                const int dn = base - r;  // 1..32 bits below the current word
-                if (dn < 32) cw |= bits >> dn;
-                flush();
-                --cm;
-                cw = dn < 32 ? bits << (32 - dn) : bits;
-            }
+        bits = lane == trip - base ? word : bits;
+        if (trip == base) {
+            emit();
+            // the chunk below sees this chunk's two lowest trips as its top
+            const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 0);
+            const uint32_t t1 = (uint32_t)__builtin_amdgcn_readlane((int)bits, 1);
+            bits = lane == kChunk ? t0 : lane == kChunk + 1 ? t1 : bits;
+            base -= kChunk;
         }
     };
 
@@ -494,7 +495,6 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
         });
         if (!more) break;
     }
-    flush();  // word 0
 }
 
 // Job of PB `idx` of a stream (Sec. III-A geometry; stream mode).

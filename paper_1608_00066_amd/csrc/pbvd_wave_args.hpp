@@ -38,7 +38,6 @@ struct Args {
     const uint8_t *syms;     // symbols; stream mode: stage 0 of the stream
     uint8_t *out;            // packed decoded bits
     uint32_t *out_words;     // zeroed word staging (atomic output) or null
-    int64_t out_bytes;       // bytes of `out` (direct output bound)
     int32_t *final_pm;       // [PB][2^V] normalized final metrics or null
     uint32_t *sp;            // survivor scratch, sp_wave_dwords per wave
     int64_t sp_wave_dwords;

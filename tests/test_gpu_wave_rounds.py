@@ -23,7 +23,7 @@ def test_trip_edges(K):
     W = V * (32 // V)
     rng = np.random.default_rng(100 + K)
     for terminated in (True, False):
-        for T in (V + 1, W - 1, W, W + 1, W + V + 1, 2 * W, 3 * W - 1, 3 * W, 4 * W + 1, 5 * W + 2):
+        for T in (V + 1, W - 1, W, W + 1, W + V + 1, 2 * W, 3 * W - 1, 3 * W, 4 * W + 1, 5 * W + 2, 62 * W, 125 * W + 3):
             n = T - (V if terminated else 0)
             if n < 1:
                 continue
