@@ -20,14 +20,14 @@
 //
 // A stage.  Each lane forms the two candidates that leave its position, the
 // one that stays (own target) and the one its partner takes, both as one
-// v_dot4_i32_i8 of the stage's R symbols (a scalar register, read from the
-// lane that loaded them) with the branch's code-word mask, accumulated onto
-// its metric; v_min_i32 then takes the partner's candidate through a DPP lane
-// swap.  The partner is lane ^ 1, 2, 7 or 8 for position bits 0..3: the swaps
+// v_dot4_i32_i8 of the stage's R symbols (the same register in every lane) with
+// the branch's code-word mask, accumulated onto its metric; v_min_i32 then
+// takes the partner's candidate through a DPP lane swap.  The partner is
+// lane ^ 1, 2, 7 or 8 for position bits 0..3: the swaps
 // DPP does in one instruction (quad permutes, half-row mirror, row rotation);
 // bits 4 and 5 use the gfx950 permlane16 / permlane32 swaps of the two
 // candidates, slot bits need no exchange.  That is 3 vector instructions per
-// stage (4 for bits 4 and 5) plus the symbol read.
+// stage (4 for bits 4 and 5).
 //
 // Branch metrics.  A branch's code word is c = (c^(1)..c^(R)) of Eq. 2; its
 // metric is sum over r of c_r q_r (the Sec. II distance minus a constant
@@ -53,13 +53,13 @@
 // tag stored for P.  A debug variant also stores the per-stage decisions of
 // every position, the survivor layout of the plain method.
 //
-// What bounds it: vector issue where several waves share a SIMD (K = 7: 26
+// What bounds it: vector issue where several waves share a SIMD (K = 7: 22
 // instructions and a few waits for 6 stages), and for a lone wave the dependent
 // chain of every stage, dot product -> swap and minimum.  Path words exchanged
 // along with the metrics, a dot product after every exchange, and symbol loads
 // that each trip waited for (12.6 instructions per stage) took twice as long:
-// 2^20 bits of K = 7 in 2,048 blocks 47.1 -> 21.4 us per decode, 2^22 bits of
-// K = 8 rate 1/3 205 -> 102 us, 4096 bits of K = 3 18.6 -> 10.9 us.
+// 2^20 bits of K = 7 in 2,048 blocks 47.1 -> 20.2 us per decode, 2^22 bits of
+// K = 8 rate 1/3 205 -> 93 us, 4096 bits of K = 3 18.6 -> 11.3 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -121,6 +121,8 @@ __device__ __forceinline__ uint32_t rotl_rt32(uint32_t u, int s) {
     return s == 0 ? u : (((u << s) | (u >> (V - s))) & ((1u << V) - 1u));
 }
 
+typedef int int4v __attribute__((ext_vector_type(4)));
+
 // The PB a wave decodes.
 struct Job {
     const uint8_t *in;   // symbols of the first forward stage
@@ -137,7 +139,7 @@ struct Job {
 // dec_wave, in the [trip][slot][position] layout of the tags.
 template <int V, bool DEC>
 __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const WaveCode &code, uint32_t *sp_wave,
-                                          uint32_t *dec_wave) {
+                                          uint32_t *dec_wave, uint32_t *q_lds) {
     constexpr int N = 1 << V;
     constexpr int SL = slots(V);
     constexpr int NL = N < kWave ? N : kWave;   // distinct positions per slot
@@ -162,9 +164,11 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
 
     // Symbols: the R symbols of stage t are packed in one dword (bytes
     // 0..R-1; the bytes above belong to the next stage and meet zero mask
-    // bytes).  Lane l holds those of stage l of two trips (2 W <= 64 stages),
-    // and each stage reads its dword into a scalar register; the two trips'
-    // loads are issued two trips ahead.  They come through a buffer resource
+    // bytes).  Lane l loads those of stage l of two trips (2 W <= 64 stages)
+    // two trips ahead, and puts them in the wave's part of the LDS, from
+    // where every lane reads four stages at a time (a read that all lanes
+    // make of one address; reading a lane's dword into a scalar register
+    // instead cost a vector instruction per stage).  They come through a buffer resource
     // that holds the dwords of the PB's own symbols: loads past it return 0
     // without a branch, so they stay in flight until they are used (a branch
     // around the end of the input made every trip wait for its loads).
@@ -190,6 +194,10 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
         const uint32_t q = __builtin_amdgcn_alignbyte(r.hi, r.lo, r.at);
         return hard ? 0x01010101u + (q & 0x01010101u) * 0xfeu : q;  // bit -> +1 / -1
     };
+
+    // the second trip's symbols start at a dword quadruple (lanes past them
+    // share the buffer's last dword, which W < 32 leaves unused)
+    uint32_t *const q_lane = q_lds + (lane < W ? lane : min(lane - W, kWave / 2 - 1) + kWave / 2);
 
     // the first trip's and the next two trips' symbols are requested before
     // the masks are formed
@@ -245,15 +253,14 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     const __amdgpu_buffer_rsrc_t sp_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         sp_wave, (short)0, (int)(pb_dwords(V, len) * 4), kBufferFlags);
 
-    // one trellis stage, the k-th of its trip (phase k mod V; symbols in lane
-    // H W + k of qv), and the tags at the end of a round.  live: the stage
-    // belongs to the PB (the first trip may start in the middle; its skipped
-    // rounds only set tags).
-    auto stage = [&](auto kc, auto hc, uint32_t qv, uint32_t (&acc)[SL], bool live) PBVD_INLINE_LAMBDA {
+    // one trellis stage, the k-th of its trip (phase k mod V), with symbols q,
+    // and the tags at the end of a round.  live: the stage belongs to the PB
+    // (the first trip may start in the middle; its skipped rounds only set
+    // tags).
+    auto stage = [&](auto kc, int q, uint32_t (&acc)[SL], bool live) PBVD_INLINE_LAMBDA {
         constexpr int k = decltype(kc)::value;
         constexpr int PH = k % V;
         if (live) {
-            const int q = __builtin_amdgcn_readlane((int)qv, decltype(hc)::value * W + k);
             if constexpr (PH < LB) {
 #pragma unroll
                 for (int s = 0; s < SL; ++s) {
@@ -319,7 +326,7 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     };
 
     // ---- forward procedure (Eq. 1) ----
-    auto run_forward = [&](auto first, auto half, uint32_t qv, int trip) PBVD_INLINE_LAMBDA {
+    auto run_forward = [&](auto first, auto half, int trip) PBVD_INLINE_LAMBDA {
         if constexpr (kEarlyRing) {
             if (trip + 1 == n_trips) {
                 // trips below the last one are stored already (a clamped
@@ -333,8 +340,15 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
         uint32_t acc[SL];
 #pragma unroll
         for (int s = 0; s < SL; ++s) acc[s] = 0;
-        static_for<0, W>([&](auto kc) PBVD_INLINE_LAMBDA {
-            stage(kc, half, qv, acc, !decltype(first)::value || decltype(kc)::value >= off);
+        const int4v *const q4 = reinterpret_cast<const int4v *>(q_lds) + decltype(half)::value * (kWave / 8);
+        static_for<0, (W + 3) / 4>([&](auto ic) PBVD_INLINE_LAMBDA {
+            constexpr int i = decltype(ic)::value;
+            const int4v q = q4[i];
+            static_for<0, W - 4 * i < 4 ? W - 4 * i : 4>([&](auto kc) PBVD_INLINE_LAMBDA {
+                constexpr int k = 4 * i + decltype(kc)::value;
+                stage(std::integral_constant<int, k>{}, q[decltype(kc)::value], acc, !decltype(first)::value || k >= off);
+                return true;
+            });
             return true;
         });
         // pass p of the trip at bits 32 - V (NP - p) ..
@@ -352,15 +366,18 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
 #pragma unroll
         for (int s = 0; s < SL; ++s) pm[s] -= ref;
     };
-    constexpr std::integral_constant<int, 0> kLow{};   // half of the lanes that hold a trip's symbols
+    constexpr std::integral_constant<int, 0> kLow{};   // half of the LDS buffer that holds a trip's symbols
     constexpr std::integral_constant<int, 1> kHigh{};
-    run_forward(std::true_type{}, kLow, make_q(raw_first), 0);  // the first trip starts at step off
+    // (one wave's LDS accesses stay in order: no wait between a buffer's last
+    // reads and its next contents)
+    *q_lane = make_q(raw_first);
+    run_forward(std::true_type{}, kLow, 0);  // the first trip starts at step off
     for (int trip = 1; trip < n_trips; trip += 2) {
-        const uint32_t qv = make_q(raw_next);
+        *q_lane = make_q(raw_next);
         raw_next = load_q((trip + 2) * W - off);  // (past the input's end: 0)
-        run_forward(std::false_type{}, kLow, qv, trip);
+        run_forward(std::false_type{}, kLow, trip);
         if (trip + 1 == n_trips) break;
-        run_forward(std::false_type{}, kHigh, qv, trip + 1);
+        run_forward(std::false_type{}, kHigh, trip + 1);
     }
 
     // ---- final metrics and traceback start (Sec. III-A; Sec. II at the end
@@ -549,7 +566,11 @@ __device__ __forceinline__ Job desc_job(const Args &a, const uint8_t *syms, int6
 // so that its loads may use the scalar unit (nothing the kernel writes
 // aliases it).
 template <int V, int MODE>
-__global__ void __launch_bounds__(256) decode_wave_kernel(const Args a, const uint8_t *__restrict__ syms) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(V <= 7 ? 8 : 4)))
+    decode_wave_kernel(const Args a, const uint8_t *__restrict__ syms) {
+    // the waves' symbol buffers (decode_pb)
+    __shared__ __align__(16) uint32_t q_block[256];
+    uint32_t *const q_lds = q_block + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) * kWave;
     const int64_t wl = (int64_t)blockIdx.x * (blockDim.x / kWave) +
                        __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (wl >= a.n_waves) return;
@@ -572,17 +593,17 @@ __global__ void __launch_bounds__(256) decode_wave_kernel(const Args a, const ui
             int ci;
             bool active;
             const Job j = desc_job(a, syms, idx, &ci, &active);
-            if (active) decode_pb<V, false>(a, j, a.codes[ci], sp, nullptr);
+            if (active) decode_pb<V, false>(a, j, a.codes[ci], sp, nullptr, q_lds);
         }
     } else if constexpr (MODE == kModeDecisions) {
         decode_pb<V, true>(a, stream_job<V>(a, syms, a.wave_begin + wl), a.codes[0], sp,
-                           a.dec_sp + wl * a.sp_wave_dwords);
+                           a.dec_sp + wl * a.sp_wave_dwords, q_lds);
     } else {
         const int64_t idx = a.wave_begin + wl;
         int ci = 0;
         bool active = true;
         const Job j = a.descs ? desc_job(a, syms, idx, &ci, &active) : stream_job<V>(a, syms, idx);
-        if (active) decode_pb<V, false>(a, j, a.codes[ci], sp, nullptr);
+        if (active) decode_pb<V, false>(a, j, a.codes[ci], sp, nullptr, q_lds);
     }
 }
 
