@@ -21,7 +21,9 @@ sys.path.insert(0, ROOT)
 
 METRIC = ("decoded Mbps, K=7 r1/2 soft, 1 MI355X (batched vs plain); serving p99 latency")
 PEAK_ALU_OPS = {16: 78.6e12, 32: 39.3e12}  # 256 CU x 64 lanes x 2.4 GHz (x2 for packed 16-bit)
-KERNEL_SOURCES = ["paper_1608_00066_amd/csrc/pbvd_kernel.hpp",
+KERNEL_SOURCES = ["paper_1608_00066_amd/csrc/pbvd_tags.hpp",
+                  "paper_1608_00066_amd/csrc/pbvd_decode_kernels.hpp",
+                  "paper_1608_00066_amd/csrc/pbvd_kernel.hpp",
                   "paper_1608_00066_amd/csrc/pbvd_code_inst.hip"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "decode_kernel_k7_d512_2p27_traffic.txt")
 

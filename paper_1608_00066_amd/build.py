@@ -25,6 +25,8 @@ HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 # -packed-fp32-ops: keep hipcc from forming packed fp32 instructions
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          # the metric bounds of the register kernels are found at compile time
+          "-fconstexpr-steps=50000000",
           "-I", INCLUDE, "-I", CSRC]
 
 

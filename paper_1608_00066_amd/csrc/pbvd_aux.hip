@@ -45,8 +45,7 @@ __global__ void unpack_survivors_kernel(SurvivorView v, uint8_t *dec) {
         const int64_t f1 = d0 + v.D + v.L > v.T ? v.T : d0 + v.D + v.L;
         uint8_t bit = 0;
         if (d0 + row < f1) {
-            const int pw = kWave >> v.lb;  // PBs per wave
-            const WavePlace wp = wave_place(b, v.pb_first, v.b_lo, v.b_hi, v.n_head, v.n_fold, v.n_int_waves, pw);
+            const WavePlace wp = wave_place(b, v.pb_first, v.b_lo, v.b_hi, v.n_head, v.n_fold, v.n_int_waves, kWave);
             const int64_t wave = wp.wave;
             const int slot = wp.slot;     // the PB's place in its wave
             const int i = (int)(d0 + row - f0);       // stage index inside the PB
@@ -56,12 +55,10 @@ __global__ void unpack_survivors_kernel(SurvivorView v, uint8_t *dec) {
             uint32_t w;
             int pos;
             if (NR >= 16) {
-                // a row holds the PBs of the wave one after another, each
-                // PB's NR/16 dwords in register order (a lane group stores
-                // them lane by lane, which is the same order)
+                // a row holds the PBs of the wave one after another
                 const int ndw = NR / 16;
-                w = base[(int64_t)i * pw * ndw + (int64_t)slot * ndw + (r >> 4)];
-                pos = v.byte_perm ? 16 * (r & 1) + 8 * half + ((r & 15) >> 1) : (r & 15) + 16 * half;
+                w = base[(int64_t)i * kWave * ndw + (int64_t)slot * ndw + (r >> 4)];
+                pos = (r & 15) + 16 * half;
             } else {
                 const int S = 16 / NR;
                 w = base[(int64_t)(i / S) * kWave + slot];

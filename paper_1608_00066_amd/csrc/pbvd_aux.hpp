@@ -13,8 +13,6 @@ struct SurvivorView {
     int64_t T, pb_first, pb_count;
     int64_t b_lo, b_hi, n_head, n_fold, n_int_waves;
     int32_t K, D, L;
-    int32_t byte_perm;  // survivor bit layout: 1 = byte-permute, 0 = shift
-    int32_t lb;         // 2^lb lanes per PB (64 >> lb PBs per wave)
     int32_t wave;       // 1: the state-parallel kernel's layout (one PB per
                         // slot of sp_wave_dwords, [trip][slot][lane] words)
 };

@@ -498,9 +498,9 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
     if (!b) return fail(PBVD_EINVAL, "batch is NULL");
     if (n_frames < 0 || (n_frames > 0 && !frames)) return fail(PBVD_EINVAL, "bad frame array");
     if (sym_bytes < 0 || out_bytes < 0) return fail(PBVD_EINVAL, "negative buffer size");
-    // codes that leave the lanes per PB open: one lane per PB when the PBs
-    // of the launch give every SIMD a wave, the largest lane group otherwise
-    // (the two codes of a registered pair share a launch: their PBs count
+    // codes that leave the lanes per PB open: usually one lane per PB when the
+    // PBs of the launch give every SIMD a wave and the largest lane group
+    // otherwise, or the cheapest width (the two codes of a registered pair share a launch: their PBs count
     // together, and they take one width so that they do share it)
     CodeSet cs = b->cs;
     {
@@ -523,7 +523,11 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
                 top = std::min(top, max_lb(cs.codes[cj]));
                 break;
             }
-            cs.lb[ci] = ceil_div(n, pbvd::kWave) >= 1024 ? 0 : top;
+            auto waves = [&](int lb) { return ceil_div(n, pbvd::kWave >> lb); };
+            const int usual = waves(0) >= 1024 ? 0 : top;
+            cs.lb[ci] = usual == 0 && cs.codes[ci].K <= 7
+                            ? 0
+                            : cheapest_lb(cs.codes[ci].K, top, usual, device_simds(b->device), waves);
         }
     }
     WorkList wl;

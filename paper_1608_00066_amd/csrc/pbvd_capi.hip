@@ -123,12 +123,19 @@ pbvd_status ensure_buffer(uint32_t **buf, size_t *have, size_t need, const char 
     return PBVD_OK;
 }
 
-// Survivor dwords of one wave slot: every forward stage of a PB (at most
-// D + 2L) is stored, one row per stage (or per few stages for small
-// trellises); a row holds 64 >> lb PBs.
-int64_t slot_dwords(const pbvd_code &c, int lb) {
+// Survivor dwords of one wave slot: a row per forward stage of a PB (at most
+// D + 2L; one per few stages for small trellises); a row holds 64 >> lb PBs.
+// The tag body stores whole groups of four stages, those from the first traced
+// stage on: at most D + L + 6 stages of the same size per stage.
+int64_t row_slot_dwords(const pbvd_code &c, int lb) {
     const int64_t rows = ceil_div((int64_t)c.D + 2 * (int64_t)c.L, pbvd::survivor_row_stages(c.K)) + 1;
     return ceil_div(rows * (pbvd::kWave >> lb) * pbvd::survivor_row_dwords(c.K), 64) * 64;
+}
+int64_t slot_dwords(const pbvd_code &c, int lb) {
+    const int64_t slot = row_slot_dwords(c, lb);
+    if (!pbvd::tag_body_used(c.K, c.pm_bits)) return slot;
+    const int64_t rows = (int64_t)c.D + c.L + 6;
+    return std::max(slot, ceil_div(rows * (pbvd::kWave >> lb) * pbvd::survivor_row_dwords(c.K), 64) * 64);
 }
 
 int requested_lb(const pbvd_code &c) {
@@ -218,6 +225,13 @@ int max_lb(const pbvd_code &c) {
     int lb = 0;
     while (lb < 3 && pbvd::lanes_allowed(c.K, c.pm_bits, lb + 1)) ++lb;
     return lb;
+}
+
+int64_t device_simds(int device) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) cus = 256;
+    (void)hipGetLastError();
+    return 4 * (int64_t)cus;
 }
 
 int64_t workspace_budget_bytes() {
@@ -430,6 +444,11 @@ void fold_fetch_bounds(const pbvd_code &c, const CallGeometry &g, int32_t *i_saf
 
 namespace {
 
+// a wave slot of the tag body can be a few rows longer than the row count that
+// the static scratch's limit is stated in (slot_dwords, overlaps below 5
+// stages): the scratch has this much more
+constexpr size_t kStaticScratchPad = 16 << 10;
+
 // Device scratch of one decode in flight: survivor rows of one launch and the
 // output staging words (used when D % 32 != 0 or the output is unaligned).
 // A fixed workspace is carved from the library's static scratch: it is
@@ -453,7 +472,7 @@ void free_workspace(Workspace &w) {
 // Survivor area / output staging of at least `need` bytes.
 pbvd_status ws_survivors(Workspace &ws, size_t need) {
     if (!ws.fixed) return ensure_buffer(&ws.sp, &ws.sp_bytes, need, "survivors");
-    if (need > ws.sp_bytes)
+    if (need > ws.sp_bytes + kStaticScratchPad)
         return fail(PBVD_EINVAL, "survivors of one launch need %zu bytes, the static scratch has %zu", need,
                     ws.sp_bytes);
     return PBVD_OK;
@@ -491,7 +510,7 @@ namespace {
 // on holds one copy from the moment the library's code object is loaded
 // until the process ends; calls on one device share it.
 constexpr size_t kStaticScratchBytes = PBVD_STATIC_SCRATCH_BYTES;
-__device__ __align__(256) uint32_t scratch[kStaticScratchBytes / 4];
+__device__ __align__(256) uint32_t scratch[(kStaticScratchBytes + kStaticScratchPad) / 4];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -527,7 +546,8 @@ struct pbvd_plan {
     int ndw;                  // survivor dwords per stored row
     int row_stages;           // stages per stored row
     int64_t budget_bytes;     // survivor workspace limit
-    int64_t n_simd;           // SIMDs of the device (4 per compute unit)
+    int64_t device_simd;      // SIMDs of the device
+    int64_t n_simd;           // the same, as the edge-folding rule takes it
     Workspace ws;             // pbvd_decode / pbvd_decode_ex
     PipeStream pipe[kMaxPipeStreams];
 };
@@ -536,29 +556,41 @@ namespace {
 
 // Waves (or PBs of the wave kernel) of one launch: as many survivor slots of
 // sp_wave_dwords as the budget holds, at least one; a fixed workspace holds
-// what fits it (possibly none).
-int64_t launch_limit(const pbvd_plan *p, const Workspace &ws, int64_t sp_wave_dwords) {
+// what fits it (possibly none), counted in slots of stated_dwords, with the
+// pad behind it for slots that are longer.
+int64_t launch_limit(const pbvd_plan *p, const Workspace &ws, int64_t sp_wave_dwords, int64_t stated_dwords) {
     int64_t w = p->budget_bytes / (sp_wave_dwords * 4);
     if (w < 1) w = 1;
-    if (ws.fixed) w = std::min<int64_t>(w, (int64_t)(ws.sp_bytes / (size_t)(sp_wave_dwords * 4)));
+    if (ws.fixed) {
+        w = std::min<int64_t>(w, (int64_t)(ws.sp_bytes / (size_t)(stated_dwords * 4)));
+        w = std::min<int64_t>(w, (int64_t)((ws.sp_bytes + kStaticScratchPad) / (size_t)(sp_wave_dwords * 4)));
+    }
     return w;
 }
+int64_t launch_limit(const pbvd_plan *p, const Workspace &ws, int64_t sp_wave_dwords) {
+    return launch_limit(p, ws, sp_wave_dwords, sp_wave_dwords);
+}
 
-// Lanes per PB of one call: the code's choice, or else
+// Lanes per PB of one call: the code's choice, or else the wave kernel up to
+// wave_max_pbs PBs, and beyond them usually
 //   one lane per PB for trellises of at most 64 states (32 packed registers)
-//   when that gives 4 waves per SIMD (4096): enough to hide latency;
+//   when that gives 4 waves per SIMD (4096);
 //   pairs of lanes where the code allows them when that gives every SIMD a
-//   wave (fewer registers per lane, so more waves hide each other's latency);
-//   the largest group the code allows otherwise (short streams).
-int call_lb(const pbvd_plan *p, int64_t n_bits, int64_t pb_first, int64_t pb_count) {
+//   wave;
+//   the largest group the code allows otherwise (short streams);
+// another width where it makes better use of the SIMDs' last turn.  The fixed
+// workspace keeps the usual rule, which its capacity was stated by.
+int call_lb(const pbvd_plan *p, int64_t n_bits, int64_t pb_first, int64_t pb_count, bool fixed_ws) {
     const int req = requested_lb(p->code);
     if (req >= 0) return req;
     // PBVD_MAP_LANES keeps the register kernel whatever the PB count
     if (p->code_idx < 0 || (p->code.mapping != PBVD_MAP_LANES && pb_count <= p->wave_max_pbs)) return kWaveLb;
     const int top = max_lb(p->code);
     if (top == 0) return 0;
-    if (p->code.K <= 7 && call_geometry(p->code, n_bits, pb_first, pb_count, 0).n_waves >= 4096) return 0;
-    return call_geometry(p->code, n_bits, pb_first, pb_count, 1).n_waves >= 1024 ? 1 : top;
+    auto waves = [&](int lb) { return call_geometry(p->code, n_bits, pb_first, pb_count, lb).n_waves; };
+    const int usual = p->code.K <= 7 && waves(0) >= 4096 ? 0 : waves(1) >= 1024 ? 1 : top;
+    if (fixed_ws) return usual;
+    return cheapest_lb(p->code.K, top, usual, p->device_simd, [&](int lb) { return ceil_div(pb_count, pbvd::kWave >> lb); });
 }
 
 pbvd_status validate_call(const pbvd_plan *p, const void *d_syms, int64_t n_bits, int64_t pb_first,
@@ -575,10 +607,10 @@ pbvd_status validate_call(const pbvd_plan *p, const void *d_syms, int64_t n_bits
 }
 
 // The state-parallel kernel for one call: one wave per PB, in launches of
-// as many PBs as the survivor workspace holds.
+// as many PBs as the survivor workspace holds (at_least whatever its size).
 pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t n_bits,
                             int64_t pb_first, int64_t pb_count, uint8_t *d_out, int32_t *d_final_pm,
-                            hipStream_t stream, CallGeometry *geo_out, bool single_launch) {
+                            hipStream_t stream, CallGeometry *geo_out, bool single_launch, int64_t at_least = 0) {
     const pbvd_code &c = p->code;
     const int64_t D = c.D;
     const int64_t T = n_bits + (c.terminated ? c.K - 1 : 0);
@@ -593,7 +625,7 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     const int64_t slot = wave_slot_dwords(c);
     // single_launch (the debug survivor export): each wave also stores its
     // per-stage decisions, after the tags of all waves
-    const int64_t per_launch = launch_limit(p, ws, single_launch ? 2 * slot : slot);
+    const int64_t per_launch = std::max(at_least, launch_limit(p, ws, single_launch ? 2 * slot : slot));
     if (per_launch < 1)
         return fail(PBVD_EINVAL, "one PB's survivors (%lld bytes) do not fit the static scratch",
                     (long long)(slot * 4));
@@ -730,7 +762,12 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
                        hipStream_t stream, CallGeometry *geo_out, bool single_launch,
                        int *lb_out = nullptr) {
     const pbvd_code &c = p->code;
-    const int lb = call_lb(p, n_bits, pb_first, pb_count);
+    int lb = call_lb(p, n_bits, pb_first, pb_count, ws.fixed);
+    // final metrics of a block that starts from the known state and ends
+    // before every state is reached: the unreached states' are those of the
+    // 32-bit metrics (the tag body takes forced upper branches there)
+    const int64_t first_len = std::min<int64_t>(n_bits + (c.terminated ? c.K - 1 : 0), (int64_t)c.D + c.L);
+    if (lb <= 3 && d_final_pm && pbvd::tag_body_used(c.K, c.pm_bits) && first_len < c.K - 1) lb = kWaveLb;
     if (lb == kWaveLb) {
         if (lb_out) *lb_out = lb;
         return run_decode_wave(p, ws, d_syms, n_bits, pb_first, pb_count, d_out, d_final_pm, stream,
@@ -746,7 +783,7 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
     if (geo_out) *geo_out = g;
     if (lb_out) *lb_out = lb;
     if (pb_count == 0) return PBVD_OK;
-    const int64_t per_launch = launch_limit(p, ws, sp_wave_dwords);
+    const int64_t per_launch = launch_limit(p, ws, sp_wave_dwords, row_slot_dwords(c, lb));
     if (per_launch < 1)
         return fail(PBVD_EINVAL, "one wave's survivors (%lld bytes) do not fit the static scratch",
                     (long long)(sp_wave_dwords * 4));
@@ -832,11 +869,7 @@ pbvd_status pbvd_create(const pbvd_code *code, pbvd_plan **out) {
     p->ndw = pbvd::survivor_row_dwords(c.K);
     p->row_stages = pbvd::survivor_row_stages(c.K);
     p->budget_bytes = workspace_budget_bytes();
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess || cus < 1)
-        cus = 256;
-    (void)hipGetLastError();
-    p->n_simd = 4 * (int64_t)cus;
+    p->device_simd = p->n_simd = device_simds(p->device);
     // the wave kernel runs a PB 64 lanes wide; the register kernel is faster
     // once a call has enough PBs to fill the device with lanes
     p->wave_max_pbs = c.K <= 7 ? 16384 : 8192;
@@ -908,7 +941,7 @@ pbvd_status pbvd_decode(pbvd_plan *p, const void *d_syms, int64_t n_bits, uint8_
 
 int32_t pbvd_call_lanes(const pbvd_plan *p, int64_t n_bits, int64_t pb_first, int64_t pb_count) {
     if (!p || n_bits < 1 || pb_first < 0 || pb_count < 0) return 0;
-    const int lb = call_lb(p, n_bits, pb_first, pb_count);
+    const int lb = call_lb(p, n_bits, pb_first, pb_count, p->ws.fixed);
     return lb == kGroupLb ? 1 << p->code.R : 1 << lb;
 }
 
@@ -953,12 +986,39 @@ pbvd_status pbvd_debug_survivors(pbvd_plan *p, const void *d_syms, int64_t n_bit
     int lb = 0;
     st = run_decode(p, p->ws, d_syms, n_bits, pb_first, pb_count, d_out_bits, nullptr, s, &g, true, &lb);
     if (st != PBVD_OK || pb_count == 0) return st;
+    if (lb <= 3 && pbvd::tag_body_used(p->code.K, p->code.pm_bits)) {
+        // the tag body keeps four decisions of the survivors, not every
+        // state's: the state-parallel kernel's debug variant gives those, in
+        // parts whose output starts on whole words (the same bits again)
+        const int64_t slot = wave_slot_dwords(p->code);
+        const int64_t part = std::max<int64_t>(launch_limit(p, p->ws, 2 * slot) / 32, 1) * 32;
+        for (int64_t b0 = 0; b0 < pb_count; b0 += part) {
+            const int64_t n = std::min(part, pb_count - b0);
+            st = run_decode_wave(p, p->ws, d_syms, n_bits, pb_first + b0, n, d_out_bits + b0 * p->code.D / 8, nullptr, s,
+                                 &g, true, n);
+            if (st != PBVD_OK) return st;
+            pbvd::SurvivorView v{};
+            v.sp = p->ws.sp + n * slot;
+            v.wave = 1;
+            v.sp_wave_dwords = slot;
+            v.T = g.T;
+            v.pb_first = pb_first + b0;
+            v.pb_count = n;
+            v.K = p->code.K;
+            v.D = p->code.D;
+            v.L = p->code.L;
+            hipError_t e = pbvd::unpack_survivors(v, d_dec + b0 * ((int64_t)v.D + v.L) * (1 << (v.K - 1)), s);
+            if (e != hipSuccess) return fail_hip(e, "survivor expansion launch");
+        }
+        hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
+        return PBVD_OK;
+    }
     pbvd::SurvivorView v{};
     // the state-parallel kernel's per-stage decisions follow its tags
     v.sp = lb == kWaveLb ? p->ws.sp + pb_count * wave_slot_dwords(p->code) : p->ws.sp;
     v.wave = lb == kWaveLb ? 1 : 0;
     v.sp_wave_dwords = lb == kWaveLb ? wave_slot_dwords(p->code) : slot_dwords(p->code, lb);
-    v.lb = lb;
     v.T = g.T;
     v.pb_first = pb_first;
     v.pb_count = pb_count;
@@ -970,7 +1030,6 @@ pbvd_status pbvd_debug_survivors(pbvd_plan *p, const void *d_syms, int64_t n_bit
     v.K = p->code.K;
     v.D = p->code.D;
     v.L = p->code.L;
-    v.byte_perm = (p->code.pm_bits == 16 && p->code.K >= 6) ? 1 : 0;
     hipError_t e = pbvd::unpack_survivors(v, d_dec, s);
     if (e != hipSuccess) return fail_hip(e, "survivor expansion launch");
     e = hipStreamSynchronize(s);

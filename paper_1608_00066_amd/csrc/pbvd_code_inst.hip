@@ -1,5 +1,6 @@
 // Decoder kernels of one registered code.  Compiled once per code with
 // -DPBVD_CODE_IDX=<index>, so the per-code kernels build in parallel.
+#include "pbvd_decode_kernels.hpp"
 #include "pbvd_registry.hpp"
 
 #ifndef PBVD_CODE_IDX

@@ -77,6 +77,37 @@ int64_t slot_dwords(const pbvd_code &c, int lb);
 int requested_lb(const pbvd_code &c);
 // The largest lane group a code supports.
 int max_lb(const pbvd_code &c);
+// SIMDs of a device (4 per compute unit).
+int64_t device_simds(int device);
+
+// The width (lanes per PB = 1 << lb, at most top) of a launch: the usual one,
+// or the one with the shortest launch where that saves more than a twentieth.
+// Waves of one SIMD share it, so a launch takes base + turn * (the waves of
+// the fullest SIMD).  More lanes per PB make a wave shorter and cost lane
+// exchanges.  Microseconds at 512 + 12 (K-1) stages, 16-bit metrics, R = 2
+// (K = 7, 8) or 3 (K = 9); other block lengths and R scale both terms alike.
+// Measured at 16Ki / 32Ki / 48Ki / 64Ki / 96Ki PBs, by lanes per PB:
+//   K=7  1: 188 192 196 211 350   2: 132 140 213 217 302
+//   K=8  1: 371 388 406 468 723   2: 219 245 374 393 577   4: 155 227 320 411 591
+//   K=9  1: 741 758 778 831 1575  2: 426 466 780 829 1188  4: 277 460 644 830 1196
+//        8: 330 590 847 1104 1619 (4Ki: 204, where 4 lanes take 259)
+// K = 7 at 2048 waves of one lane: 374 and 385, at 4096 706 and 720.
+template <class Waves>
+int cheapest_lb(int K, int top, int usual, int64_t n_simd, Waves waves) {
+    struct Cost {
+        int base, turn;
+    };
+    static constexpr Cost kCost[3][4] = {{{46, 165}, {57, 83}},                          // K <= 7
+                                         {{58, 410}, {73, 172}, {67, 89}},               // K = 8
+                                         {{0, 825}, {110, 357}, {93, 184}, {84, 127}}};  // K = 9
+    const Cost *const cost = kCost[K <= 7 ? 0 : K - 7];
+    auto us = [&](int lb) { return cost[lb].base + cost[lb].turn * ceil_div(waves(lb), n_simd); };
+    int best = usual;
+    int64_t limit = us(usual) * 20;
+    for (int lb = top; lb >= 0; --lb)
+        if (lb != usual && us(lb) * 21 < limit) best = lb, limit = us(lb) * 21;
+    return best;
+}
 
 // Survivor workspace limit of one plan or batch (PBVD_WORKSPACE_MB, default 8 GiB).
 int64_t workspace_budget_bytes();

@@ -2,6 +2,7 @@
 // one launch).  Compiled once per pair and input kind with
 // -DPBVD_PAIR_IDX=<index> -DPBVD_PAIR_KIND=<kSoftI8 or kHardU8>, so the
 // units build in parallel.
+#include "pbvd_decode_kernels.hpp"
 #include "pbvd_registry.hpp"
 
 #if !defined(PBVD_PAIR_IDX) || !defined(PBVD_PAIR_KIND)
