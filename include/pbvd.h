@@ -262,16 +262,19 @@ void pbvd_destroy(pbvd_plan *p);
  * A batch decodes many frames (each a separate stream in the sense of
  * Sec. III-A: its own PBs, its own start and end).  The PBs of all frames
  * are packed regardless of frame boundaries, so thousands of short frames
- * fill the GPU as well as one long stream does; per code mapping:
+ * fill the GPU as well as one long stream does.  Codes that leave the mapping
+ * open (PBVD_MAP_AUTO, lanes_per_pb 0) take the state-parallel kernel while
+ * the frames of a pbvd_batch_set_frames have few PBs, the register kernel
+ * otherwise.  Per mapping:
  *   register kernel (PBVD_MAP_LANES / AUTO): tiles of 64 >> lb PBs of one
  *     code, one launch per code, except that the two codes of a pair the
  *     library registers (K=7 (171,133) with (133,171,165)) share one launch
  *     when they have the same lanes per PB, 16-bit metrics and input kind
  *     (each tile decoded with its own code);
  *   state-parallel kernel (PBVD_MAP_WAVE): the PBs of every such code of one
- *     K in ONE persistent launch, longest first, waves taking PBs from work
- *     counters (one per XCD) that a fill kernel zeroes at the start of each
- *     decode;
+ *     K in ONE launch, longest first: a wave per PB where the device holds
+ *     them all, else persistent waves that take PBs from work counters (one
+ *     per XCD) that a fill kernel zeroes at the start of each decode;
  *   group mapping (PBVD_MAP_GROUP): tiles of 64 PBs, one launch per code.
  * The launches run on forked streams.  Every frame's output is identical to
  * decoding that frame alone with pbvd_decode and the same code parameters.

@@ -48,6 +48,11 @@ pbvd_status make_code_set(const pbvd_code *codes, int32_t n, CodeSet *out, int a
 
 namespace {
 
+// A registered code whose mapping and lanes per PB are the library's choice.
+bool auto_mapping(const CodeSet &cs, int ci) {
+    return cs.idx[ci] >= 0 && requested_lb(cs.codes[ci]) < 0 && cs.codes[ci].mapping != PBVD_MAP_LANES;
+}
+
 // Waves per workgroup of a tile launch: 4 (PBVD_TILE_WAVES_PER_BLOCK = 1, 2
 // or 4 overrides it).
 int tile_waves_per_block() {
@@ -394,8 +399,11 @@ pbvd_status launch_fused(const CodeSet &cs, int K, const FusedGroup &g, const ui
                          int64_t sym_bytes, uint8_t *d_out, const pbvd::LaneDesc *d_descs, uint32_t *sp,
                          int64_t waves, uint32_t *counter, hipStream_t stream) {
     if (g.n_descs == 0) return PBVD_OK;
-    // a kernel, not a memset node: the launch may be captured into a graph
-    hipError_t e = pbvd::fill_u32(counter, pbvd::wave::kCounters * pbvd::wave::kCounterStride, 0u, stream);
+    // a wave for every PB: the waves need no counters to share the PBs out
+    const bool persist = waves < g.n_descs;
+    hipError_t e = hipSuccess;
+    // (a kernel, not a memset node: the launch may be captured into a graph)
+    if (persist) e = pbvd::fill_u32(counter, pbvd::wave::kCounters * pbvd::wave::kCounterStride, 0u, stream);
     if (e != hipSuccess) return fail_hip(e, "work counter reset");
     pbvd::WaveLaunchRequest req{};
     pbvd::wave::Args &a = req.args;
@@ -405,7 +413,7 @@ pbvd_status launch_fused(const CodeSet &cs, int K, const FusedGroup &g, const ui
     a.sp = sp;
     a.sp_wave_dwords = g.sp_wave_dwords;
     a.descs = d_descs + g.desc_begin;
-    a.counter = counter;
+    a.counter = persist ? counter : nullptr;
     a.n_items = g.n_descs;
     for (int k = 0; k < g.n_codes; ++k) a.codes[k] = wave_code(cs.codes[g.codes[k]]);
     a.wave_begin = 0;
@@ -508,8 +516,21 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
         for (int64_t f = 0; f < n_frames; ++f)
             if (frames[f].code >= 0 && frames[f].code < cs.n && frames[f].n_bits > 0)
                 pbs[frames[f].code] += ceil_div(frames[f].n_bits, cs.codes[frames[f].code].D);
+        // All of them on the wave mapping while the batch has few PBs: each
+        // code's as a share of the most that its K decodes faster there, the
+        // shares together at most one (the launches run side by side).
+        double share = 0;
+        for (int ci = 0; ci < cs.n; ++ci)
+            if (auto_mapping(cs, ci) && pbs[ci] > 0) {
+                const int64_t most = wave_max_pbs(cs.codes[ci].K);
+                share += most > 0 ? (double)pbs[ci] / (double)most : 2.0;
+            }
         for (int ci = 0; ci < cs.n; ++ci) {
             if (requested_lb(cs.codes[ci]) >= 0 || cs.idx[ci] < 0) continue;
+            if (share <= 1.0 && auto_mapping(cs, ci)) {
+                cs.lb[ci] = kWaveLb;
+                continue;
+            }
             int64_t n = pbs[ci];
             int top = max_lb(cs.codes[ci]);
             for (int cj = 0; cj < cs.n; ++cj) {

@@ -227,6 +227,16 @@ int max_lb(const pbvd_code &c) {
     return lb;
 }
 
+// The wave kernel runs a PB 64 lanes wide; the register kernel is faster once
+// a call has enough PBs to fill the device with lanes.  Microseconds, wave and
+// register kernel, D = 512: K = 7 16Ki PBs 91 and 132, 24Ki 132 and 134;
+// K = 8 8Ki 92 and 135, 16Ki 172 and 155; K = 9 rate 1/3 4Ki 126 and 204, 8Ki
+// 219 and 212 (D = 64: 70 and 66).
+int64_t wave_max_pbs(int K) {
+    if (const char *env = getenv("PBVD_WAVE_MAX_PBS")) return atoll(env);
+    return K <= 7 ? 16384 : 8192;
+}
+
 int64_t device_simds(int device) {
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) cus = 256;
@@ -870,10 +880,7 @@ pbvd_status pbvd_create(const pbvd_code *code, pbvd_plan **out) {
     p->row_stages = pbvd::survivor_row_stages(c.K);
     p->budget_bytes = workspace_budget_bytes();
     p->device_simd = p->n_simd = device_simds(p->device);
-    // the wave kernel runs a PB 64 lanes wide; the register kernel is faster
-    // once a call has enough PBs to fill the device with lanes
-    p->wave_max_pbs = c.K <= 7 ? 16384 : 8192;
-    if (const char *env = getenv("PBVD_WAVE_MAX_PBS")) p->wave_max_pbs = atoll(env);
+    p->wave_max_pbs = wave_max_pbs(c.K);
     {
         // set up the static scratch of this device (pbvd_decode_ex_noalloc);
         // a failure here is reported by that call, which tries again

@@ -77,6 +77,9 @@ int64_t slot_dwords(const pbvd_code &c, int lb);
 int requested_lb(const pbvd_code &c);
 // The largest lane group a code supports.
 int max_lb(const pbvd_code &c);
+// Auto mapping: the wave kernel up to this many PBs of constraint length K
+// (PBVD_WAVE_MAX_PBS overrides it).
+int64_t wave_max_pbs(int K);
 // SIMDs of a device (4 per compute unit).
 int64_t device_simds(int device);
 
