@@ -59,7 +59,8 @@
 // along with the metrics, a dot product after every exchange, and symbol loads
 // that each trip waited for (12.6 instructions per stage) took twice as long:
 // 2^20 bits of K = 7 in 2,048 blocks 47.1 -> 20.2 us per decode, 2^22 bits of
-// K = 8 rate 1/3 205 -> 93 us, 4096 bits of K = 3 18.6 -> 11.3 us.
+// K = 8 rate 1/3 205 -> 93 us, 4096 bits of K = 3 18.6 -> 11.3 us, 2,048 blocks
+// of 512 bits of K = 9 rate 1/3 118 -> 55 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -461,19 +462,15 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
                 P = ((uint32_t)__builtin_amdgcn_readlane((int)hw[0], l) >> sh) & (uint32_t)(N - 1);
             } else {
                 // the slot round's tag (top V - 6 bits of the pass) names the
-                // slot whose lane round led here
-                uint32_t f[SL];
+                // slot whose lane round led here; a pass's tags of all slots,
+                // a byte each, are put together before the lane is known
+                // (a choice between scalars became a table in scratch memory)
+                uint32_t f = 0;
 #pragma unroll
-                for (int s = 0; s < SL; ++s)
-                    f[s] = ((uint32_t)__builtin_amdgcn_readlane((int)hw[s], l) >> sh) & (uint32_t)(N - 1);
-                auto of_slot = [&](uint32_t slot) PBVD_INLINE_LAMBDA {
-                    uint32_t v = f[0];
-#pragma unroll
-                    for (int s = 1; s < SL; ++s) v = slot == (uint32_t)s ? f[s] : v;
-                    return v;
-                };
-                const uint32_t slot = of_slot(P >> 6) >> 6;
-                P = slot << 6 | (of_slot(slot) & 63u);
+                for (int s = 0; s < SL; ++s) f |= (hw[s] >> sh & (uint32_t)(N - 1)) << (8 * s);
+                f = (uint32_t)__builtin_amdgcn_readlane((int)f, l);
+                const uint32_t slot = (f >> (P >> 6 << 3) & (uint32_t)(N - 1)) >> 6;
+                P = slot << 6 | (f >> (slot << 3) & 63u);
             }
             return true;
         });
