@@ -84,7 +84,7 @@ def build(jobs: int | None = None, verbose: bool = False, csrc: str = CSRC,
                       os.path.join(build_dir, "wave_k%d.o" % k), ["-DPBVD_WAVE_K=%d" % k]))
         units.append((os.path.join(csrc, "pbvd_group_inst.hip"),
                       os.path.join(build_dir, "group_k%d.o" % k), ["-DPBVD_GROUP_K=%d" % k]))
-    for name in ("pbvd_capi", "pbvd_batch", "pbvd_server", "pbvd_aux"):
+    for name in ("pbvd_capi", "pbvd_batch", "pbvd_server", "pbvd_aux", "pbvd_wave_mixed"):
         units.append((os.path.join(csrc, name + ".hip"), os.path.join(build_dir, name + ".o"), []))
 
     def newest_dep(src):

@@ -48,6 +48,12 @@ pbvd_status make_code_set(const pbvd_code *codes, int32_t n, CodeSet *out, int a
 
 namespace {
 
+// The longest list that one launch of every K takes, per SIMD.  PBs of K = 3,
+// 7 and 9 (D = 64) in one launch and in one per K on forked streams, us: 1357
+// PBs 16.8 and 53, 3997 18.7 and 53.8, 7958 32 and 57.6; of K = 3 and 5, 15654
+// PBs 30 and 44.
+constexpr int64_t kMixedWavesPerSimd = 32;
+
 // A registered code whose mapping and lanes per PB are the library's choice.
 bool auto_mapping(const CodeSet &cs, int ci) {
     return cs.idx[ci] >= 0 && requested_lb(cs.codes[ci]) < 0 && cs.codes[ci].mapping != PBVD_MAP_LANES;
@@ -127,16 +133,15 @@ pbvd_status build_work_list(const CodeSet &cs, const pbvd_frame *frames, int64_t
         // one descriptor list per K over all its state-parallel codes, the
         // longest PBs first (the persistent waves take them in this order,
         // so the longest finish first and the short ones fill the tail)
-        for (int K = kMinK; K <= kMaxK; ++K) {
+        for (int K = kMaxK; K >= kMinK; --K) {
             FusedGroup &fg = wl->fused[K - kMinK];
             std::vector<PbRec> v;
             for (int ci = 0; ci < cs.n; ++ci) {
                 if (cs.lb[ci] != kWaveLb || cs.codes[ci].K != K) continue;
-                const int slot = fg.n_codes++;
-                fg.codes[slot] = ci;
+                fg.codes[fg.n_codes++] = ci;
                 fg.sp_wave_dwords = std::max(fg.sp_wave_dwords, wave_slot_dwords(cs.codes[ci]));
                 for (PbRec r : per_code[ci]) {
-                    r.flags |= slot << pbvd::wave::kDescCodeShift;
+                    r.flags |= ci << pbvd::wave::kDescCodeShift;
                     v.push_back(r);
                 }
                 per_code[ci].clear();
@@ -415,13 +420,13 @@ pbvd_status launch_fused(const CodeSet &cs, int K, const FusedGroup &g, const ui
     a.descs = d_descs + g.desc_begin;
     a.counter = persist ? counter : nullptr;
     a.n_items = g.n_descs;
-    for (int k = 0; k < g.n_codes; ++k) a.codes[k] = wave_code(cs.codes[g.codes[k]]);
+    for (int k = 0; k < g.n_codes; ++k) a.codes[g.codes[k]] = wave_code(cs.codes[g.codes[k]]);
     a.wave_begin = 0;
     a.n_waves = std::max<int64_t>(1, std::min(waves, g.n_descs));
     req.grid = (unsigned)ceil_div(a.n_waves, pbvd::kBlockThreads / pbvd::kWave);
     req.stream = stream;
-    e = launch_wave(K, req);
-    if (e != hipSuccess) return fail_hip(e, "persistent wave kernel launch");
+    e = g.mixed ? pbvd::launch_wave_mixed(req) : launch_wave(K, req);
+    if (e != hipSuccess) return fail_hip(e, "wave kernel launch");
     return PBVD_OK;
 }
 
@@ -462,6 +467,28 @@ struct pbvd_batch {
 };
 
 namespace {
+
+// The state-parallel PBs of every K as one group (the first) where they are of
+// more than one K and few: at most kMixedWavesPerSimd waves per SIMD, with a
+// survivor slot each inside a code's share of the budget.
+void mix_waves(const CodeSet &cs, int64_t n_simd, int64_t budget, WorkList *wl) {
+    FusedGroup m{};
+    m.mixed = true;
+    int n_k = 0;
+    for (int K = kMaxK; K >= kMinK; --K) {
+        const FusedGroup &fg = wl->fused[K - kMinK];
+        if (fg.n_descs == 0) continue;
+        if (n_k++ == 0) m.desc_begin = fg.desc_begin;  // the largest K's come first
+        for (int k = 0; k < fg.n_codes; ++k) m.codes[m.n_codes++] = fg.codes[k];
+        m.n_descs += fg.n_descs;
+        m.sp_wave_dwords = std::max(m.sp_wave_dwords, fg.sp_wave_dwords);
+    }
+    if (n_k < 2 || m.n_descs > kMixedWavesPerSimd * n_simd || m.n_descs * m.sp_wave_dwords * 4 > budget / cs.n ||
+        getenv("PBVD_PERSISTENT_WAVES"))
+        return;
+    for (FusedGroup &fg : wl->fused) fg = FusedGroup{};
+    wl->fused[0] = m;
+}
 
 constexpr int64_t kCounterDwords = pbvd::wave::kCounters * pbvd::wave::kCounterStride;
 
@@ -508,8 +535,9 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
     if (sym_bytes < 0 || out_bytes < 0) return fail(PBVD_EINVAL, "negative buffer size");
     // codes that leave the lanes per PB open: usually one lane per PB when the
     // PBs of the launch give every SIMD a wave and the largest lane group
-    // otherwise, or the cheapest width (the two codes of a registered pair share a launch: their PBs count
-    // together, and they take one width so that they do share it)
+    // otherwise, or the cheapest width (the two codes of a registered pair
+    // share a launch: their PBs count together, and they take one width so
+    // that they do share it)
     CodeSet cs = b->cs;
     {
         int64_t pbs[kMaxCodes] = {};
@@ -518,16 +546,25 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
                 pbs[frames[f].code] += ceil_div(frames[f].n_bits, cs.codes[frames[f].code].D);
         // All of them on the wave mapping while the batch has few PBs: each
         // code's as a share of the most that its K decodes faster there, the
-        // shares together at most one (the launches run side by side).
+        // shares together at most one; two where they are of several K and
+        // one launch takes them (tiles need a launch per code, and forked
+        // streams cost 20 us each): 18185 PBs of K = 3, 7 and 9, D = 64, 65 us
+        // there and 103 in tiles.
         double share = 0;
+        int64_t open = 0;
+        int ks = 0;  // bit K: there are PBs of that K
         for (int ci = 0; ci < cs.n; ++ci)
             if (auto_mapping(cs, ci) && pbs[ci] > 0) {
                 const int64_t most = wave_max_pbs(cs.codes[ci].K);
                 share += most > 0 ? (double)pbs[ci] / (double)most : 2.0;
+                open += pbs[ci];
+                ks |= 1 << cs.codes[ci].K;
             }
+        const bool one_launch = (ks & (ks - 1)) != 0 && open <= kMixedWavesPerSimd * device_simds(b->device);
+        const double share_max = one_launch ? 2.0 : 1.0;
         for (int ci = 0; ci < cs.n; ++ci) {
             if (requested_lb(cs.codes[ci]) >= 0 || cs.idx[ci] < 0) continue;
-            if (share <= 1.0 && auto_mapping(cs, ci)) {
+            if (share <= share_max && auto_mapping(cs, ci)) {
                 cs.lb[ci] = kWaveLb;
                 continue;
             }
@@ -593,12 +630,18 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
     // persistent launch needs an area per resident wave only, whatever its
     // PB count (fewer waves when the budget is short).
     const int64_t budget = workspace_budget_bytes();
+    mix_waves(b->cs, device_simds(b->device), budget, &wl);
     int64_t fused_waves[kMaxK - kMinK + 1] = {};
     int64_t full = 0;
     for (int ci = 0; ci < b->cs.n; ++ci) full += wl.groups[ci].n_tiles * wl.groups[ci].sp_wave_dwords * 4;
     for (int K = kMinK; K <= kMaxK; ++K) {
         const FusedGroup &fg = wl.fused[K - kMinK];
         if (fg.n_descs == 0) continue;
+        if (fg.mixed) {
+            fused_waves[K - kMinK] = fg.n_descs;
+            full += fg.n_descs * fg.sp_wave_dwords * 4;
+            continue;
+        }
         int64_t res = resident_waves(K);
         if (res <= 0) return fail(PBVD_EHIP, "occupancy query of the K=%d persistent kernel failed", K);
         // PBVD_PERSISTENT_WAVES caps the waves (tests: many PBs per wave)
@@ -621,7 +664,8 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
         const FusedGroup &fg = wl.fused[K - kMinK];
         int64_t &w = fused_waves[K - kMinK];
         if (fg.n_descs == 0) continue;
-        if (full > budget) w = std::min(w, std::max<int64_t>(1, budget / b->cs.n / (fg.sp_wave_dwords * 4)));
+        if (full > budget && !fg.mixed)
+            w = std::min(w, std::max<int64_t>(1, budget / b->cs.n / (fg.sp_wave_dwords * 4)));
         fused_sp_off[K - kMinK] = total;
         total += w * fg.sp_wave_dwords;
     }

@@ -196,6 +196,7 @@ pbvd::wave::WaveCode wave_code(const pbvd_code &c) {
     for (int r = 0; r < 4; ++r) w.gen[r] = r < c.R ? c.gen[r] : 0u;
     w.R = c.R;
     w.kind = c.input_kind;
+    w.K = c.K;
     return w;
 }
 

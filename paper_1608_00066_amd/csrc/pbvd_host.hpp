@@ -158,12 +158,13 @@ struct TileGroup {
 };
 
 // The PBs of every state-parallel code of one constraint length, for one
-// persistent launch: descriptors [desc_begin, + n_descs), longest first,
-// each naming its code by its slot in `codes` (flag bits from
+// launch: descriptors [desc_begin, + n_descs), longest first, each naming its
+// code by its index in the code set (flag bits from
 // pbvd::wave::kDescCodeShift).
 struct FusedGroup {
     int n_codes = 0;
-    int codes[kMaxCodes];           // code set index of each slot
+    int codes[kMaxCodes];           // code set indices
+    bool mixed = false;             // the PBs of every K, for one launch
     int64_t desc_begin = 0, n_descs = 0;
     int64_t sp_wave_dwords = 0;     // the largest slot of its codes
 };

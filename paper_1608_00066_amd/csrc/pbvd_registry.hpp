@@ -99,6 +99,8 @@ struct WaveLaunchRequest {
 // Implemented by the translation unit compiled for constraint length K.
 template <int K>
 hipError_t launch_wave(const WaveLaunchRequest &req);
+// The same for a work list whose codes have different K: a wave per PB.
+hipError_t launch_wave_mixed(const WaveLaunchRequest &req);
 // Group-mapped kernel (a workgroup of 2^R waves per tile of 64 PBs).
 struct GroupLaunchRequest {
     group::GroupArgs args;

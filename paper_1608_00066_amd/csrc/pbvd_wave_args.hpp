@@ -19,11 +19,13 @@ __host__ __device__ constexpr int64_t pb_dwords(int V, int64_t len) {
 }
 
 // A code of the state-parallel kernel: the kernel takes the generators, the
-// rate and the input kind at run time, so one kernel per K decodes them all.
+// rate and the input kind at run time, so one kernel per K decodes them all
+// (and one kernel those of every K, decode_wave_mixed_kernel).
 struct WaveCode {
     uint32_t gen[4];   // gen[r] bit k = g_k of Eq. 2; 0 for r >= R
     int32_t R;         // symbols per stage (2..4)
     int32_t kind;      // kSoftI8 / kHardU8
+    int32_t K;
 };
 constexpr int kMaxWaveCodes = 16;
 // Work counters of a persistent launch: one per XCD, a cache line apart.

@@ -1,7 +1,7 @@
 """The mapping a batch chooses for codes that leave it open: the wave mapping
-for few PBs (one list launch per K where a wave is there for every PB,
-persistent waves otherwise), tiles of the register kernel for many.  Every
-frame against the CPU oracle (bits are equal: no tolerance)."""
+for few PBs (one list launch for all K, or for one K, where a wave is there for
+every PB, persistent waves otherwise), tiles of the register kernel for many.
+Every frame against the CPU oracle (bits are equal: no tolerance)."""
 import pytest
 
 from test_gpu_batch import check_batch, log, pbvd, torch  # noqa: F401  (fixtures)
@@ -21,7 +21,8 @@ def test_batch_auto_mapping(torch, pbvd, monkeypatch, path, frames, hi):  # noqa
         monkeypatch.setenv("PBVD_PERSISTENT_WAVES", "3")  # fewer waves than PBs: work counters
     if path == "tiles":
         monkeypatch.setenv("PBVD_WAVE_MAX_PBS", "0")
-    codes = ALL_K if frames > 1 else ALL_K[4:5]
+    # one K, two (the smallest and the largest) or all
+    codes = {1: ALL_K[4:5], 9: [ALL_K[0], ALL_K[7]], 120: ALL_K}[frames]
     log("batch auto mapping: %s, %d frames up to %d bits" % (path, frames, hi))
     _, _, _, _, info = check_batch(torch, pbvd, codes, frames, 1, hi, seed=frames)
     if path != "tiles":
