@@ -209,7 +209,9 @@ pbvd_status pbvd_decode_host(pbvd_plan *p, const void *h_syms, int64_t n_bits, u
  * mapping for codes outside the registry and for calls of fewer PBs than a
  * threshold (PBVD_WAVE_MAX_PBS overrides it); else one lane for K <= 7 when
  * that gives 4096 waves of 64 PBs, else pairs of lanes where the code allows
- * them when that gives 1024 waves, else the largest group the code allows.
+ * them when that gives 1024 waves, else the largest group the code allows --
+ * or another of these widths where its waves fill the SIMDs so much better
+ * that the launch is a twentieth shorter (pbvd_decode_ex_noalloc: not).
  * 0 on invalid arguments. */
 int32_t pbvd_call_lanes(const pbvd_plan *p, int64_t n_bits, int64_t pb_first, int64_t pb_count);
 

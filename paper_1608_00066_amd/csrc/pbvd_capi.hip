@@ -469,6 +469,8 @@ struct Workspace {
     size_t sp_bytes = 0;
     uint32_t *words = nullptr;
     size_t words_bytes = 0;
+    uint32_t *edges = nullptr;  // kOutEdges words, 0 between calls
+    size_t edges_bytes = 0;
     bool fixed = false;
 };
 
@@ -476,6 +478,7 @@ void free_workspace(Workspace &w) {
     if (!w.fixed) {
         if (w.sp) (void)hipFree(w.sp);
         if (w.words) (void)hipFree(w.words);
+        if (w.edges) (void)hipFree(w.edges);
     }
     w = Workspace{};
 }
@@ -494,6 +497,78 @@ pbvd_status ws_staging(Workspace &ws, size_t need) {
         return fail(PBVD_EINVAL, "output staging needs %zu bytes, the static scratch has %zu", need,
                     ws.words_bytes);
     return PBVD_OK;
+}
+
+// Where a stream call's bits go.
+struct Output {
+    int mode = pbvd::kOutDirect;
+    uint32_t *words = nullptr;
+    int64_t bits = 0;
+};
+
+// Zeroed words for the boundaries between n_pbs PBs: cleared once, in the
+// call's stream (while it is captured, on a stream of their own: the graph is
+// not run yet); every launch leaves them 0.
+pbvd_status ws_edges(Workspace &ws, int64_t n_pbs, hipStream_t stream) {
+    const size_t need = (size_t)(n_pbs + 1) * 4;
+    if (ws.edges_bytes >= need) return PBVD_OK;
+    pbvd_status st = ensure_buffer(&ws.edges, &ws.edges_bytes, ceil_div((int64_t)need, 4096) * 4096, "block boundaries");
+    if (st != PBVD_OK) return st;
+    const int64_t n = (int64_t)(ws.edges_bytes / 4);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(stream, &cap);
+    if (e == hipSuccess && cap == hipStreamCaptureStatusNone) {
+        e = pbvd::fill_u32(ws.edges, n, 0u, stream);
+    } else if (e == hipSuccess) {
+        hipStream_t s = nullptr;
+        e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+        if (e == hipSuccess) e = pbvd::fill_u32(ws.edges, n, 0u, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (s) (void)hipStreamDestroy(s);
+    }
+    if (e == hipSuccess) return PBVD_OK;
+    ws.edges_bytes = 0;  // cleared before its next use
+    return fail_hip(e, "clearing the block boundaries");
+}
+
+// Plain stores where the PBs own whole bytes.  Other PBs of more than 8 bits
+// exchange the bits of the bytes they share (edges: the kernel can; the fixed
+// workspace has no words that stay 0).  Else the words are OR-ed into a zeroed
+// staging buffer, which end_output copies.
+pbvd_status begin_output(Workspace &ws, int64_t D, int64_t out_bits, int64_t n_pbs, const uint8_t *d_out, bool edges,
+                         hipStream_t stream, Output *o) {
+    o->bits = out_bits;
+    if (D % 32 == 0 && ((uintptr_t)d_out & 3u) == 0) {
+        o->mode = pbvd::kOutDirect;
+    } else if (D % 8 == 0) {
+        o->mode = pbvd::kOutBytes;
+    } else if (edges && D > 8 && !ws.fixed) {
+        pbvd_status st = ws_edges(ws, n_pbs, stream);
+        if (st != PBVD_OK) return st;
+        o->mode = pbvd::kOutEdges;
+        o->words = ws.edges;
+    } else {
+        const int64_t nwords = ceil_div(out_bits, 32) + 2;
+        pbvd_status st = ws_staging(ws, (size_t)nwords * 4);
+        if (st != PBVD_OK) return st;
+        hipError_t e = pbvd::fill_u32(ws.words, nwords, 0u, stream);
+        if (e != hipSuccess) return fail_hip(e, "zero-fill launch");
+        o->mode = pbvd::kOutAtomic;
+        o->words = ws.words;
+    }
+    return PBVD_OK;
+}
+
+pbvd_status end_output(Workspace &ws, const Output &o, uint8_t *d_out, hipStream_t stream) {
+    if (o.mode != pbvd::kOutAtomic) return PBVD_OK;
+    const hipError_t e = pbvd::words_to_bytes(ws.words, d_out, ceil_div(o.bits, 8), stream);
+    return e == hipSuccess ? PBVD_OK : fail_hip(e, "output copy launch");
+}
+
+// A launch of the call failed: its PBs' boundary words may be left set.
+pbvd_status failed_launch(Workspace &ws, hipError_t e, const char *what) {
+    ws.edges_bytes = 0;
+    return fail_hip(e, what);
 }
 
 constexpr int kMaxPipeStreams = 8;
@@ -649,20 +724,15 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     if (st != PBVD_OK) return st;
     const int64_t end_bit = std::min(n_bits, (pb_first + pb_count) * D);
     const int64_t out_bits = end_bit - pb_first * D;
-    const int64_t out_bytes = ceil_div(out_bits, 8);
-    const bool direct = (D % 32 == 0) && (((uintptr_t)d_out & 3u) == 0);
-    if (!direct) {
-        const int64_t nwords = ceil_div(out_bits, 32) + 2;
-        st = ws_staging(ws, (size_t)nwords * 4);
-        if (st != PBVD_OK) return st;
-        hipError_t e = pbvd::fill_u32(ws.words, nwords, 0u, stream);
-        if (e != hipSuccess) return fail_hip(e, "zero-fill launch");
-    }
+    Output o;
+    st = begin_output(ws, D, out_bits, pb_count, d_out, true, stream, &o);
+    if (st != PBVD_OK) return st;
     pbvd::WaveLaunchRequest req{};
     pbvd::wave::Args &a = req.args;
     a.syms = (const uint8_t *)d_syms;
     a.out = d_out;
-    a.out_words = direct ? nullptr : ws.words;
+    a.out_words = o.words;
+    a.out_bits = o.bits;
     a.final_pm = d_final_pm;
     a.sp = ws.sp;
     a.sp_wave_dwords = slot;
@@ -672,7 +742,7 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     a.D = c.D;
     a.L = c.L;
     a.terminated = c.terminated;
-    a.out_mode = direct ? pbvd::kOutDirect : pbvd::kOutAtomic;
+    a.out_mode = o.mode;
     a.descs = nullptr;
     a.dec_sp = single_launch ? ws.sp + launch_pbs * slot : nullptr;
     a.codes[0] = wave_code(c);
@@ -683,13 +753,9 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
         a.n_waves = std::min(launch_pbs, pb_count - w0);
         req.grid = (unsigned)ceil_div(a.n_waves, waves_per_block);
         hipError_t e = launch_wave(c.K, req);
-        if (e != hipSuccess) return fail_hip(e, "wave decode kernel launch");
+        if (e != hipSuccess) return failed_launch(ws, e, "wave decode kernel launch");
     }
-    if (!direct) {
-        hipError_t e = pbvd::words_to_bytes(ws.words, d_out, out_bytes, stream);
-        if (e != hipSuccess) return fail_hip(e, "output copy launch");
-    }
-    return PBVD_OK;
+    return end_output(ws, o, d_out, stream);
 }
 
 // The group-mapped kernel for one call: tiles of 64 consecutive PBs, in
@@ -722,23 +788,18 @@ pbvd_status run_decode_group(pbvd_plan *p, Workspace &ws, const void *d_syms, in
     const int64_t end_bit = std::min(n_bits, (pb_first + pb_count) * D);
     const int64_t out_bits = end_bit - pb_first * D;
     const int64_t out_bytes = ceil_div(out_bits, 8);
-    const bool direct = (D % 32 == 0) && (((uintptr_t)d_out & 3u) == 0);
-    if (!direct) {
-        const int64_t nwords = ceil_div(out_bits, 32) + 2;
-        st = ws_staging(ws, (size_t)nwords * 4);
-        if (st != PBVD_OK) return st;
-        hipError_t e = pbvd::fill_u32(ws.words, nwords, 0u, stream);
-        if (e != hipSuccess) return fail_hip(e, "zero-fill launch");
-    }
+    Output o;
+    st = begin_output(ws, D, out_bits, pb_count, d_out, false, stream, &o);
+    if (st != PBVD_OK) return st;
     pbvd::GroupLaunchRequest req{};
     pbvd::group::GroupArgs &a = req.args;
     a = p->gt;
     a.syms = (const uint8_t *)d_syms;
     a.in_end = a.syms + T * c.R;
     a.out = d_out;
-    a.out_words = direct ? nullptr : ws.words;
+    a.out_words = o.words;
     a.out_bytes = out_bytes;
-    a.out_mode = direct ? pbvd::kOutDirect : pbvd::kOutAtomic;
+    a.out_mode = o.mode;
     a.kind = c.input_kind;
     a.final_pm = d_final_pm;
     a.sp = ws.sp;
@@ -760,11 +821,7 @@ pbvd_status run_decode_group(pbvd_plan *p, Workspace &ws, const void *d_syms, in
         hipError_t e = launch_group_kernel(c.K, req);
         if (e != hipSuccess) return fail_hip(e, "group decode kernel launch");
     }
-    if (!direct) {
-        hipError_t e = pbvd::words_to_bytes(ws.words, d_out, out_bytes, stream);
-        if (e != hipSuccess) return fail_hip(e, "output copy launch");
-    }
-    return PBVD_OK;
+    return end_output(ws, o, d_out, stream);
 }
 
 // Runs the decode kernels of one call; fills *geo with the decomposition.
@@ -808,20 +865,16 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
     if (st != PBVD_OK) return st;
 
     const int64_t out_bytes = ceil_div(g.out_bits, 8);
-    const bool direct = (c.D % 32 == 0) && (((uintptr_t)d_out & 3u) == 0);
-    if (!direct) {
-        const int64_t nwords = ceil_div(g.out_bits, 32) + 2;
-        st = ws_staging(ws, (size_t)nwords * 4);
-        if (st != PBVD_OK) return st;
-        hipError_t e = pbvd::fill_u32(ws.words, nwords, 0u, stream);
-        if (e != hipSuccess) return fail_hip(e, "zero-fill launch");
-    }
+    Output o;
+    st = begin_output(ws, c.D, g.out_bits, pb_count, d_out, pbvd::tag_body_used(c.K, c.pm_bits), stream, &o);
+    if (st != PBVD_OK) return st;
 
     pbvd::LaunchRequest req{};
     pbvd::KernelArgs &a = req.args;
     a.syms = (const uint8_t *)d_syms;
     a.out = d_out;
-    a.out_words = direct ? nullptr : ws.words;
+    a.out_words = o.words;
+    a.out_bits = o.bits;
     a.final_pm = d_final_pm;
     a.sp = ws.sp;
     a.n = n_bits;
@@ -838,7 +891,7 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
     a.D = c.D;
     a.L = c.L;
     a.terminated = c.terminated;
-    a.direct_out = direct ? 1 : 0;
+    a.out_mode = o.mode;
     req.pm_bits = c.pm_bits;
     req.input_kind = c.input_kind;
     req.lb = lb;
@@ -849,13 +902,9 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
         a.n_waves = (g.n_waves - w0) < launch_waves ? (g.n_waves - w0) : launch_waves;
         req.grid = (unsigned)ceil_div(a.n_waves, waves_per_block);
         hipError_t e = kLaunchTable[p->code_idx](req);
-        if (e != hipSuccess) return fail_hip(e, "decode kernel launch");
+        if (e != hipSuccess) return failed_launch(ws, e, "decode kernel launch");
     }
-    if (!direct) {
-        hipError_t e = pbvd::words_to_bytes(ws.words, d_out, out_bytes, stream);
-        if (e != hipSuccess) return fail_hip(e, "output copy launch");
-    }
-    return PBVD_OK;
+    return end_output(ws, o, d_out, stream);
 }
 
 }  // namespace

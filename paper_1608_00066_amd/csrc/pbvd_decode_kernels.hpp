@@ -68,10 +68,11 @@ __global__ void __launch_bounds__(256)
 
     uint32_t *const sp = a.sp + wave_local * a.sp_wave_dwords;
     WaveJob j;
-    j.out_mode = a.direct_out ? kOutDirect : kOutAtomic;
+    j.out_mode = a.out_mode;
     j.out = a.out;
     j.out_bytes = a.out_bytes;
     j.out_words = a.out_words;
+    j.out_bits = a.out_bits;
     j.in_end = a.syms + a.T * R;
 
     if (wave == 0 && a.n_fold > 0) {
@@ -110,6 +111,7 @@ __global__ void __launch_bounds__(256)
         j.active = active;
         j.store0_uniform = false;
         j.out_bit0 = (b - a.pb_first) * D;
+        j.edge = (int)(b - a.pb_first);
         j.pm_out = nullptr;
         wave_body<C, P, KIND, true, LB>(j, sp, a.sp_wave_dwords);
         return;
@@ -161,6 +163,7 @@ __global__ void __launch_bounds__(256)
     j.active = active;
     j.store0_uniform = true;
     j.out_bit0 = (b - a.pb_first) * D;
+    j.edge = (int)(b - a.pb_first);
     j.pm_out = a.final_pm ? a.final_pm + (b - a.pb_first) * N : nullptr;
     wave_body<C, P, KIND, false, LB>(j, sp, a.sp_wave_dwords);
 }
@@ -196,6 +199,8 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int64_t wave_local,
     j.out = a.out;
     j.out_bytes = 0;
     j.out_words = nullptr;
+    j.out_bits = 0;
+    j.edge = 0;
     j.out_bit0 = d.out_bit;
     j.pm_out = nullptr;
 

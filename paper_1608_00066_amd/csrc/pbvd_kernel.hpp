@@ -66,7 +66,7 @@ __device__ __forceinline__ bool static_for(F &&f) {
 struct KernelArgs {
     const uint8_t *syms;    // T*R received symbols, stage-major
     uint8_t *out;           // packed decoded bits (direct path)
-    uint32_t *out_words;    // zeroed word buffer (atomic path) or null
+    uint32_t *out_words;    // kOutAtomic: zeroed words; kOutEdges: the boundaries' words; else null
     int32_t *final_pm;      // [pb_count][N] normalized final metrics or null
     uint32_t *sp;           // survivor scratch, sp_wave_dwords per wave slot
     int64_t n;              // information bits of the stream
@@ -79,10 +79,11 @@ struct KernelArgs {
     int64_t wave_begin;     // first wave (interior waves first, then edge waves)
     int64_t n_waves;        // waves in this launch
     int64_t out_bytes;      // bytes of `out`
+    int64_t out_bits;       // bits of the call
     int64_t sp_wave_dwords; // survivor dwords per wave slot
     int32_t D, L;
     int32_t terminated;
-    int32_t direct_out;     // 1: plain stores into out, 0: atomic OR into out_words
+    int32_t out_mode;       // kOutDirect / kOutAtomic / kOutBytes / kOutEdges
     int32_t fold_i_safe;    // first wave with folded PBs: last trip start whose wide fetch is in bounds
     int32_t fold_wide;      // first wave with folded PBs: every wide fetch is in bounds
 };
@@ -394,7 +395,7 @@ __device__ __forceinline__ int rotr_rt(int u, int s) {
 // forward ACS with survivor-row stores, final metrics, then traceback with
 // packed output, for the 64 PBs of one wave.
 // ---------------------------------------------------------------------------
-enum { kOutDirect = 0, kOutAtomic = 1, kOutBytes = 2 };
+enum { kOutDirect = 0, kOutAtomic = 1, kOutBytes = 2, kOutEdges = 3 };
 
 struct WaveJob {
     // wave-uniform
@@ -403,11 +404,12 @@ struct WaveJob {
     int i_safe;          // last trip start whose wide fetch is in bounds (-1: none)
     bool fetch_safe;     // every wide fetch of the wave stays in bounds
     bool need_final;     // some lane needs its final metrics
-    int out_mode;        // kOutDirect / kOutAtomic / kOutBytes
+    int out_mode;        // kOutDirect / kOutAtomic / kOutBytes / kOutEdges
     const uint8_t *in_end;
     uint8_t *out;
     int64_t out_bytes;   // kOutDirect bound
-    uint32_t *out_words; // kOutAtomic staging
+    uint32_t *out_words; // kOutAtomic staging, kOutEdges words
+    int64_t out_bits;    // kOutEdges: bits of the call
     // per lane
     const uint8_t *in;   // symbols of the lane's first forward stage
     int my_len, my_store0, my_dec_end;
@@ -416,8 +418,22 @@ struct WaveJob {
     bool active;
     bool store0_uniform; // VARLEN: every lane's first traced stage is store0_min
     int64_t out_bit0;    // output bit position of the lane's first decoded bit
+    int edge;            // kOutEdges: the lane's PB, counted from the call's first
     int32_t *pm_out;     // final-metric row or null
 };
+
+// kOutEdges: PBs of D % 8 != 0 bits (D > 8) share the byte at each boundary
+// between two of them.  Both bring their bits of it to the boundary's word,
+// which is 0 between launches: the first leaves them there, the second takes
+// them, writes the byte and clears the word.  (Zeroing a word buffer before
+// the decode, OR-ing every word into it and copying it out took two more
+// launches, 12 us a call.)
+__device__ __forceinline__ void put_edge(uint32_t *word, uint8_t *byte, uint32_t bits) {
+    const uint32_t other = atomicOr(word, bits | 0x100u);
+    if (other == 0) return;
+    *byte = (uint8_t)(other | bits);
+    atomicExch(word, 0u);
+}
 
 // VARLEN: lanes may run fewer stages than the wave (batch tiles).  All lanes
 // start at stage 0 with their own initial metrics; a lane's stages past its

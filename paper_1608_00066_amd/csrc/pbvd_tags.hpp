@@ -661,6 +661,8 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
     //      stored.  Input bits are collected in words of 32 virtual stages; a
     //      lane's output words start at ds and span two of them. ----
     const bool writer = j.active && ell == 0;
+    // kOutEdges: bits up to the PB's first whole byte
+    const int head = j.out_mode == kOutEdges ? (int)(-j.out_bit0 & 7) : 0;
     auto put_word = [&](uint32_t v, int rel) PBVD_INLINE_LAMBDA {
         const int nb = n_dec - rel < 32 ? n_dec - rel : 32;
         if (nb < 32) v &= (1u << nb) - 1u;
@@ -676,17 +678,26 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
             if (nb == 32 && (((uintptr_t)ob & 3u) == 0)) {
                 *reinterpret_cast<uint32_t *>(ob) = v;
             } else {
-                for (int bb = 0; bb < ((nb + 7) >> 3); ++bb) ob[bb] = (uint8_t)(v >> (8 * bb));
+                const bool shared = j.out_mode == kOutEdges && (nb & 7) != 0 && bitpos + nb != j.out_bits;
+                for (int bb = 0; bb < ((nb + (shared ? 0 : 7)) >> 3); ++bb) ob[bb] = (uint8_t)(v >> (8 * bb));
+                if (shared) put_edge(j.out_words + j.edge + 1, ob + (nb >> 3), v >> (nb & ~7) & 0xffu);
             }
         }
+    };
+    // the PB's bits before its first whole byte (kOutEdges)
+    auto put_head = [&](uint32_t v) PBVD_INLINE_LAMBDA {
+        v &= (1u << (n_dec < head ? n_dec : head)) - 1u;
+        put_edge(j.out_words + j.edge, j.out + (j.out_bit0 >> 3), v << (j.out_bit0 & 7));
     };
     uint32_t word = 0, above = 0;
     auto emit = [&](int g) PBVD_INLINE_LAMBDA {
         // word holds the stages from 4 g up; the word of 32 that contains it
         const int v0 = (g & ~7) * kTagBits;
         const uint32_t cur = word << ((g & 7) * kTagBits);
-        const int rel = v0 + (ds & 31) - ds;  // a multiple of 32
-        if (writer && rel >= 0 && rel < n_dec) put_word(__builtin_amdgcn_alignbit(above, cur, (uint32_t)ds & 31u), rel);
+        const int rel = v0 + ((ds + head) & 31) - ds;  // head and a multiple of 32
+        const uint32_t v = __builtin_amdgcn_alignbit(above, cur, (uint32_t)(ds + head) & 31u);
+        if (writer && rel >= 0 && rel < n_dec) put_word(v, rel);
+        if (j.out_mode == kOutEdges && writer && rel < 0 && rel > -32) put_head(v >> -rel);
         above = cur;
         word = 0;
     };
@@ -792,6 +803,7 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
         });
         if (!more) break;
     }
+    if (j.out_mode == kOutEdges) emit((g0 & ~7) - 8);  // heads in the word below
 }
 
 }  // namespace pbvd

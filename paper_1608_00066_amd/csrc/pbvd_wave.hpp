@@ -133,6 +133,7 @@ struct Job {
     bool known;          // starts from encoder state 0
     bool argmin;         // traceback from the least-metric state
     int64_t out_bit0;    // output bit of the first decoded stage
+    int edge;            // kOutEdges: the PB, counted from the call's first
     int32_t *pm_out;     // final metrics or null
 };
 
@@ -420,22 +421,30 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
     constexpr int kChunk = kWave - 2;  // lanes 62, 63: the two trips above the chunk
     int base = trip_bot + (n_trips - 1 - trip_bot) / kChunk * kChunk;
     uint32_t bits = 0;
+    // kOutEdges: bits up to the PB's first whole byte
+    const int head = a.out_mode == kOutEdges ? (int)(-j.out_bit0 & 7) : 0;
     auto emit = [&]() PBVD_INLINE_LAMBDA {
         // word m of the PB starts at virtual stage first + 32 m; this
-        // chunk's words start in trips base .. base + kChunk - 1
-        const int first = j.store0 + off;
+        // chunk's words start in trips base .. base + kChunk - 1.  Word -1
+        // is the head, the stages before first.
+        const int first = j.store0 + off + head;
         const int lowest = base * W - first;
-        const int m = (lowest > 0 ? (lowest + 31) >> 5 : 0) + lane;
-        const int at = 32 * m - lowest;  // from the chunk's first stage
+        const int m = (lowest > 0 ? (lowest + 31) >> 5 : head > 0 ? -1 : 0) + lane;
+        const int at = (m < 0 ? -head : 32 * m) - lowest;  // from the chunk's first stage
         const int i = at / W, sh = at - i * W;
         uint32_t v = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i, (int)bits) >> sh;
         v |= (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i + 4, (int)bits) << 1 << (W - 1 - sh);
         const uint32_t top = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * i + 8, (int)bits);
         if (2 * W - sh < 32) v |= top << (2 * W - sh);
-        const int nb = n_dec - 32 * m < 32 ? n_dec - 32 * m : 32;
+        if (m < 0) {
+            v &= (1u << (n_dec < head ? n_dec : head)) - 1u;
+            put_edge(a.out_words + j.edge, a.out + (j.out_bit0 >> 3), v << (j.out_bit0 & 7));
+            return;
+        }
+        const int nb = n_dec - head - 32 * m < 32 ? n_dec - head - 32 * m : 32;
         if (i >= kChunk || nb <= 0) return;
         if (nb < 32) v &= (1u << nb) - 1u;
-        const int64_t bitpos = j.out_bit0 + 32 * m;
+        const int64_t bitpos = j.out_bit0 + head + 32 * m;
         if (a.out_mode == kOutAtomic) {
             const uint32_t shf = (uint32_t)(bitpos & 31);
             uint32_t *wp = a.out_words + (bitpos >> 5);
@@ -447,7 +456,9 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
         if (nb == 32 && ((uintptr_t)ob & 3u) == 0) {
             *reinterpret_cast<uint32_t *>(ob) = v;
         } else {
-            for (int bb = 0; bb < ((nb + 7) >> 3); ++bb) ob[bb] = (uint8_t)(v >> (8 * bb));
+            const bool shared = a.out_mode == kOutEdges && (nb & 7) != 0 && bitpos + nb != a.out_bits;
+            for (int bb = 0; bb < ((nb + (shared ? 0 : 7)) >> 3); ++bb) ob[bb] = (uint8_t)(v >> (8 * bb));
+            if (shared) put_edge(a.out_words + j.edge + 1, ob + (nb >> 3), v >> (nb & ~7) & 0xffu);
         }
     };
 
@@ -529,6 +540,7 @@ __device__ __forceinline__ Job stream_job(const Args &a, const uint8_t *syms, in
     j.known = f0 == 0;
     j.argmin = f1 == a.T && !a.terminated;
     j.out_bit0 = idx * D;
+    j.edge = (int)idx;
     j.pm_out = a.final_pm ? a.final_pm + idx * N : nullptr;
     return j;
 }
@@ -545,6 +557,7 @@ __device__ __forceinline__ Job desc_job(const Args &a, const uint8_t *syms, int6
     j.known = (fl & kLaneKnown) != 0;
     j.argmin = (fl & kLaneArgmin) != 0;
     j.out_bit0 = uniform64(d.out_bit);
+    j.edge = 0;
     j.pm_out = nullptr;
     *code_idx = (fl >> kDescCodeShift) & 0xff;
     *active = (fl & kLaneActive) != 0;

@@ -39,14 +39,15 @@ constexpr int kDescCodeShift = 8;
 struct Args {
     const uint8_t *syms;     // symbols; stream mode: stage 0 of the stream
     uint8_t *out;            // packed decoded bits
-    uint32_t *out_words;     // zeroed word staging (atomic output) or null
+    uint32_t *out_words;     // kOutAtomic: zeroed words; kOutEdges: the boundaries' words; else null
+    int64_t out_bits;        // kOutEdges: bits of the call
     int32_t *final_pm;       // [PB][2^V] normalized final metrics or null
     uint32_t *sp;            // survivor scratch, sp_wave_dwords per wave
     int64_t sp_wave_dwords;
     // stream mode (descs == null): PBs [pb_first + wave_begin, + n_waves)
     int64_t n, T, pb_first;
     int32_t D, L, terminated;
-    int32_t out_mode;        // kOutDirect / kOutAtomic / kOutBytes
+    int32_t out_mode;        // kOutDirect / kOutAtomic / kOutBytes / kOutEdges
     // tile mode: one descriptor per PB (lane descriptor of the batch work list)
     const LaneDesc *descs;
     int64_t wave_begin;      // first PB of this launch (relative to pb_first / descs)
