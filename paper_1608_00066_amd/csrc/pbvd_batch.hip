@@ -219,9 +219,15 @@ pbvd_status build_work_list(const CodeSet &cs, const pbvd_frame *frames, int64_t
             } else {
                 // a tile ends where the first traced stage changes: its PBs
                 // share it, so that tiles of PBs of different lengths take
-                // the phase-aligned traceback
+                // the phase-aligned traceback; and (batches) where a PB is
+                // shorter than 7/8 of the first: the trips until the last PB
+                // of a tile has begun take half as long again, and the slowest
+                // tile sets the end of a launch of one wave per SIMD (4096
+                // frames of 40 to 6144 bits, D = 208: 132 -> 115 us)
                 size_t k = i + 1;
-                while (k < e && !(v[k].flags & pbvd::kLaneArgmin) && v[k].store0 == v[i].store0) ++k;
+                while (k < e && !(v[k].flags & pbvd::kLaneArgmin) && v[k].store0 == v[i].store0 &&
+                       (!pair_tiles || 8 * v[k].len >= 7 * v[i].len))
+                    ++k;
                 e = k;
             }
             pbvd::TileHead h{};
@@ -535,9 +541,11 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
     if (sym_bytes < 0 || out_bytes < 0) return fail(PBVD_EINVAL, "negative buffer size");
     // codes that leave the lanes per PB open: usually one lane per PB when the
     // PBs of the launch give every SIMD a wave and the largest lane group
-    // otherwise, or the cheapest width (the two codes of a registered pair
-    // share a launch: their PBs count together, and they take one width so
-    // that they do share it)
+    // otherwise (K <= 7; the cheapest width for K >= 8), or the cheapest width.
+    // K = 7 rates 1/2 and 1/3 at D = 208, us with 1 and 2 lanes: 30697 PBs 107
+    // and 78, 45767 110 and 117, 62742 115 and 120, 67243 130 and 133.  The two
+    // codes of a registered pair share a launch: their PBs count together, and
+    // they take one width so that they do share it.
     CodeSet cs = b->cs;
     {
         int64_t pbs[kMaxCodes] = {};
