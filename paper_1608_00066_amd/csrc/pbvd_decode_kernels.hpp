@@ -16,8 +16,10 @@ namespace pbvd {
 #define PBVD_BIG_TRELLIS_WAVES_PER_EU 1
 #endif
 // Register target for 64 metric VGPRs per lane (a 256-state trellis on lane
-// pairs or 128 states on one lane, 16-bit metrics): three waves fit without
-// spills.
+// pairs or 128 states on one lane, 16-bit metrics).  Three waves spill some
+// registers, all outside the stage loops; with room for two K = 9 rate 1/3 on
+// pairs is 4 to 8 % faster at D = 64 (64Ki PBs 228 -> 211 us) and 1 to 3 % slower
+// on long streams of D = 512 (256Ki PBs 2962 -> 3057 us).
 #ifndef PBVD_MID_TRELLIS_WAVES_PER_EU
 #define PBVD_MID_TRELLIS_WAVES_PER_EU 3
 #endif
