@@ -507,25 +507,20 @@ struct Output {
 };
 
 // Zeroed words for the boundaries between n_pbs PBs: cleared once, in the
-// call's stream (while it is captured, on a stream of their own: the graph is
-// not run yet); every launch leaves them 0.
-pbvd_status ws_edges(Workspace &ws, int64_t n_pbs, hipStream_t stream) {
+// call's stream; every launch leaves them 0.  Nothing may be allocated while the
+// stream is captured: false then, unless the words are there already.
+pbvd_status ws_edges(Workspace &ws, int64_t n_pbs, hipStream_t stream, bool *have) {
     const size_t need = (size_t)(n_pbs + 1) * 4;
+    *have = true;
     if (ws.edges_bytes >= need) return PBVD_OK;
-    pbvd_status st = ensure_buffer(&ws.edges, &ws.edges_bytes, ceil_div((int64_t)need, 4096) * 4096, "block boundaries");
-    if (st != PBVD_OK) return st;
-    const int64_t n = (int64_t)(ws.edges_bytes / 4);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(stream, &cap);
-    if (e == hipSuccess && cap == hipStreamCaptureStatusNone) {
-        e = pbvd::fill_u32(ws.edges, n, 0u, stream);
-    } else if (e == hipSuccess) {
-        hipStream_t s = nullptr;
-        e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-        if (e == hipSuccess) e = pbvd::fill_u32(ws.edges, n, 0u, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (s) (void)hipStreamDestroy(s);
-    }
+    if (e != hipSuccess) return fail_hip(e, "capture query");
+    *have = cap == hipStreamCaptureStatusNone;
+    if (!*have) return PBVD_OK;
+    pbvd_status st = ensure_buffer(&ws.edges, &ws.edges_bytes, ceil_div((int64_t)need, 4096) * 4096, "block boundaries");
+    if (st != PBVD_OK) return st;
+    e = pbvd::fill_u32(ws.edges, (int64_t)(ws.edges_bytes / 4), 0u, stream);
     if (e == hipSuccess) return PBVD_OK;
     ws.edges_bytes = 0;  // cleared before its next use
     return fail_hip(e, "clearing the block boundaries");
@@ -533,18 +528,21 @@ pbvd_status ws_edges(Workspace &ws, int64_t n_pbs, hipStream_t stream) {
 
 // Plain stores where the PBs own whole bytes.  Other PBs of more than 8 bits
 // exchange the bits of the bytes they share (edges: the kernel can; the fixed
-// workspace has no words that stay 0).  Else the words are OR-ed into a zeroed
-// staging buffer, which end_output copies.
+// workspace has no words that stay 0, and a captured call may find none).  Else
+// the words are OR-ed into a zeroed staging buffer, which end_output copies.
 pbvd_status begin_output(Workspace &ws, int64_t D, int64_t out_bits, int64_t n_pbs, const uint8_t *d_out, bool edges,
                          hipStream_t stream, Output *o) {
     o->bits = out_bits;
+    bool words = edges && D > 8 && D % 8 != 0 && !ws.fixed;
+    if (words) {
+        pbvd_status st = ws_edges(ws, n_pbs, stream, &words);
+        if (st != PBVD_OK) return st;
+    }
     if (D % 32 == 0 && ((uintptr_t)d_out & 3u) == 0) {
         o->mode = pbvd::kOutDirect;
     } else if (D % 8 == 0) {
         o->mode = pbvd::kOutBytes;
-    } else if (edges && D > 8 && !ws.fixed) {
-        pbvd_status st = ws_edges(ws, n_pbs, stream);
-        if (st != PBVD_OK) return st;
+    } else if (words) {
         o->mode = pbvd::kOutEdges;
         o->words = ws.edges;
     } else {
