@@ -43,7 +43,9 @@
  *
  * Concurrency: decode calls are asynchronous on the given HIP stream (NULL =
  * the null stream).  A plan holds one workspace: do not run two decodes of
- * the same plan concurrently (use one plan per stream).
+ * the same plan concurrently (use one plan per stream).  A graph captured from
+ * a decode keeps the workspace of its capture: it must not be replayed after a
+ * call on the plan that needed a larger one.
  *
  * Errors: arguments are validated before anything is launched; on a
  * negative status nothing has been written to the output buffers.  No C++

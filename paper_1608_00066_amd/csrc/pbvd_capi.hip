@@ -469,8 +469,9 @@ struct Workspace {
     size_t sp_bytes = 0;
     uint32_t *words = nullptr;
     size_t words_bytes = 0;
-    uint32_t *edges = nullptr;  // kOutEdges words, 0 between calls
+    uint32_t *edges = nullptr;  // kOutEdges words
     size_t edges_bytes = 0;
+    uint32_t edge_call = 0;     // number of the last call that used them
     bool fixed = false;
 };
 
@@ -504,38 +505,51 @@ struct Output {
     int mode = pbvd::kOutDirect;
     uint32_t *words = nullptr;
     int64_t bits = 0;
+    uint32_t call = 0;
 };
 
-// Zeroed words for the boundaries between n_pbs PBs: cleared once, in the
-// call's stream; every launch leaves them 0.  Nothing may be allocated while the
-// stream is captured: false then, unless the words are there already.
-pbvd_status ws_edges(Workspace &ws, int64_t n_pbs, hipStream_t stream, bool *have) {
+// Words for the boundaries between n_pbs PBs and the number of the call
+// (pbvd_edges.hpp).  They are cleared when they are allocated and when the calls'
+// numbers start again, in the call's stream.  Nothing may be allocated while the
+// stream is captured: false then, unless the words are there; a captured call
+// clears them itself, every time it is replayed.
+pbvd_status ws_edges(Workspace &ws, int64_t n_pbs, hipStream_t stream, bool *have, uint32_t *call) {
     const size_t need = (size_t)(n_pbs + 1) * 4;
-    *have = true;
-    if (ws.edges_bytes >= need) return PBVD_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    hipError_t e = hipStreamIsCapturing(stream, &cap);
-    if (e != hipSuccess) return fail_hip(e, "capture query");
-    *have = cap == hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();  // the launches will tell
+    const bool captured = cap != hipStreamCaptureStatusNone;
+    *have = !captured || ws.edges_bytes >= need;
     if (!*have) return PBVD_OK;
-    pbvd_status st = ensure_buffer(&ws.edges, &ws.edges_bytes, ceil_div((int64_t)need, 4096) * 4096, "block boundaries");
-    if (st != PBVD_OK) return st;
-    e = pbvd::fill_u32(ws.edges, (int64_t)(ws.edges_bytes / 4), 0u, stream);
+    bool clear = captured;
+    if (!captured) {
+        if (ws.edges_bytes < need) {
+            pbvd_status st =
+                ensure_buffer(&ws.edges, &ws.edges_bytes, ceil_div((int64_t)need, 4096) * 4096, "block boundaries");
+            if (st != PBVD_OK) return st;
+            ws.edge_call = 0;
+        }
+        ws.edge_call = pbvd::edge_next_call(ws.edge_call);
+        clear = ws.edge_call == 1;
+    }
+    *call = captured ? 0 : ws.edge_call;
+    if (!clear) return PBVD_OK;
+    const hipError_t e =
+        pbvd::fill_u32(ws.edges, captured ? n_pbs + 1 : (int64_t)(ws.edges_bytes / 4), 0u, stream);
     if (e == hipSuccess) return PBVD_OK;
-    ws.edges_bytes = 0;  // cleared before its next use
+    if (!captured) ws.edge_call = 0;  // cleared before their next use
     return fail_hip(e, "clearing the block boundaries");
 }
 
 // Plain stores where the PBs own whole bytes.  Other PBs of more than 8 bits
 // exchange the bits of the bytes they share (edges: the kernel can; the fixed
-// workspace has no words that stay 0, and a captured call may find none).  Else
+// workspace has no such words, and a captured call may find none).  Else
 // the words are OR-ed into a zeroed staging buffer, which end_output copies.
 pbvd_status begin_output(Workspace &ws, int64_t D, int64_t out_bits, int64_t n_pbs, const uint8_t *d_out, bool edges,
                          hipStream_t stream, Output *o) {
     o->bits = out_bits;
     bool words = edges && D > 8 && D % 8 != 0 && !ws.fixed;
     if (words) {
-        pbvd_status st = ws_edges(ws, n_pbs, stream, &words);
+        pbvd_status st = ws_edges(ws, n_pbs, stream, &words, &o->call);
         if (st != PBVD_OK) return st;
     }
     if (D % 32 == 0 && ((uintptr_t)d_out & 3u) == 0) {
@@ -561,12 +575,6 @@ pbvd_status end_output(Workspace &ws, const Output &o, uint8_t *d_out, hipStream
     if (o.mode != pbvd::kOutAtomic) return PBVD_OK;
     const hipError_t e = pbvd::words_to_bytes(ws.words, d_out, ceil_div(o.bits, 8), stream);
     return e == hipSuccess ? PBVD_OK : fail_hip(e, "output copy launch");
-}
-
-// A launch of the call failed: its PBs' boundary words may be left set.
-pbvd_status failed_launch(Workspace &ws, hipError_t e, const char *what) {
-    ws.edges_bytes = 0;
-    return fail_hip(e, what);
 }
 
 constexpr int kMaxPipeStreams = 8;
@@ -731,6 +739,7 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     a.out = d_out;
     a.out_words = o.words;
     a.out_bits = o.bits;
+    a.edge_call = o.call;
     a.final_pm = d_final_pm;
     a.sp = ws.sp;
     a.sp_wave_dwords = slot;
@@ -751,7 +760,7 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
         a.n_waves = std::min(launch_pbs, pb_count - w0);
         req.grid = (unsigned)ceil_div(a.n_waves, waves_per_block);
         hipError_t e = launch_wave(c.K, req);
-        if (e != hipSuccess) return failed_launch(ws, e, "wave decode kernel launch");
+        if (e != hipSuccess) return fail_hip(e, "wave decode kernel launch");
     }
     return end_output(ws, o, d_out, stream);
 }
@@ -873,6 +882,7 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
     a.out = d_out;
     a.out_words = o.words;
     a.out_bits = o.bits;
+    a.edge_call = o.call;
     a.final_pm = d_final_pm;
     a.sp = ws.sp;
     a.n = n_bits;
@@ -900,7 +910,7 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
         a.n_waves = (g.n_waves - w0) < launch_waves ? (g.n_waves - w0) : launch_waves;
         req.grid = (unsigned)ceil_div(a.n_waves, waves_per_block);
         hipError_t e = kLaunchTable[p->code_idx](req);
-        if (e != hipSuccess) return failed_launch(ws, e, "decode kernel launch");
+        if (e != hipSuccess) return fail_hip(e, "decode kernel launch");
     }
     return end_output(ws, o, d_out, stream);
 }

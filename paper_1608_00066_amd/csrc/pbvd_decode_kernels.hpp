@@ -75,6 +75,7 @@ __global__ void __launch_bounds__(256)
     j.out_bytes = a.out_bytes;
     j.out_words = a.out_words;
     j.out_bits = a.out_bits;
+    j.edge_call = a.edge_call;
     j.in_end = a.syms + a.T * R;
 
     if (wave == 0 && a.n_fold > 0) {
@@ -202,6 +203,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int64_t wave_local,
     j.out_bytes = 0;
     j.out_words = nullptr;
     j.out_bits = 0;
+    j.edge_call = 0;
     j.edge = 0;
     j.out_bit0 = d.out_bit;
     j.pm_out = nullptr;

@@ -32,6 +32,8 @@
 
 #include <type_traits>
 
+#include "pbvd_edges.hpp"
+
 // Lambdas on the hot path are forced inline so that the arrays they capture
 // stay in registers.
 #define PBVD_INLINE_LAMBDA __attribute__((always_inline))
@@ -86,6 +88,7 @@ struct KernelArgs {
     int32_t out_mode;       // kOutDirect / kOutAtomic / kOutBytes / kOutEdges
     int32_t fold_i_safe;    // first wave with folded PBs: last trip start whose wide fetch is in bounds
     int32_t fold_wide;      // first wave with folded PBs: every wide fetch is in bounds
+    uint32_t edge_call;     // kOutEdges: number of the call
 };
 
 // Place of PB b in the stream kernel's waves.  Edge PBs (clipped geometry at
@@ -410,6 +413,7 @@ struct WaveJob {
     int64_t out_bytes;   // kOutDirect bound
     uint32_t *out_words; // kOutAtomic staging, kOutEdges words
     int64_t out_bits;    // kOutEdges: bits of the call
+    uint32_t edge_call;  // kOutEdges: number of the call
     // per lane
     const uint8_t *in;   // symbols of the lane's first forward stage
     int my_len, my_store0, my_dec_end;
@@ -422,17 +426,13 @@ struct WaveJob {
     int32_t *pm_out;     // final-metric row or null
 };
 
-// kOutEdges: PBs of D % 8 != 0 bits (D > 8) share the byte at each boundary
-// between two of them.  Both bring their bits of it to the boundary's word,
-// which is 0 between launches: the first leaves them there, the second takes
-// them, writes the byte and clears the word.  (Zeroing a word buffer before
-// the decode, OR-ing every word into it and copying it out took two more
-// launches, 12 us a call.)
-__device__ __forceinline__ void put_edge(uint32_t *word, uint8_t *byte, uint32_t bits) {
-    const uint32_t other = atomicOr(word, bits | 0x100u);
-    if (other == 0) return;
-    *byte = (uint8_t)(other | bits);
-    atomicExch(word, 0u);
+// kOutEdges: a PB's bits of a byte it shares (pbvd_edges.hpp).  (Zeroing a word
+// buffer before the decode, OR-ing every word into it and copying it out took
+// two more launches, 12 us a call.)
+__device__ __forceinline__ void put_edge(uint32_t *word, uint8_t *byte, uint32_t bits, uint32_t call) {
+    const uint32_t mine = edge_word(call, bits);
+    const uint32_t found = atomicExch(word, mine);
+    if (edge_second(mine, found)) *byte = (uint8_t)(found | mine);
 }
 
 // VARLEN: lanes may run fewer stages than the wave (batch tiles).  All lanes

@@ -680,14 +680,14 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
             } else {
                 const bool shared = j.out_mode == kOutEdges && (nb & 7) != 0 && bitpos + nb != j.out_bits;
                 for (int bb = 0; bb < ((nb + (shared ? 0 : 7)) >> 3); ++bb) ob[bb] = (uint8_t)(v >> (8 * bb));
-                if (shared) put_edge(j.out_words + j.edge + 1, ob + (nb >> 3), v >> (nb & ~7) & 0xffu);
+                if (shared) put_edge(j.out_words + j.edge + 1, ob + (nb >> 3), v >> (nb & ~7) & 0xffu, j.edge_call);
             }
         }
     };
     // the PB's bits before its first whole byte (kOutEdges)
     auto put_head = [&](uint32_t v) PBVD_INLINE_LAMBDA {
         v &= (1u << (n_dec < head ? n_dec : head)) - 1u;
-        put_edge(j.out_words + j.edge, j.out + (j.out_bit0 >> 3), v << (j.out_bit0 & 7));
+        put_edge(j.out_words + j.edge, j.out + (j.out_bit0 >> 3), v << (j.out_bit0 & 7), j.edge_call);
     };
     uint32_t word = 0, above = 0;
     auto emit = [&](int g) PBVD_INLINE_LAMBDA {

@@ -438,7 +438,7 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
         if (2 * W - sh < 32) v |= top << (2 * W - sh);
         if (m < 0) {
             v &= (1u << (n_dec < head ? n_dec : head)) - 1u;
-            put_edge(a.out_words + j.edge, a.out + (j.out_bit0 >> 3), v << (j.out_bit0 & 7));
+            put_edge(a.out_words + j.edge, a.out + (j.out_bit0 >> 3), v << (j.out_bit0 & 7), a.edge_call);
             return;
         }
         const int nb = n_dec - head - 32 * m < 32 ? n_dec - head - 32 * m : 32;
@@ -458,7 +458,7 @@ __device__ __forceinline__ void decode_pb(const Args &a, const Job &j, const Wav
         } else {
             const bool shared = a.out_mode == kOutEdges && (nb & 7) != 0 && bitpos + nb != a.out_bits;
             for (int bb = 0; bb < ((nb + (shared ? 0 : 7)) >> 3); ++bb) ob[bb] = (uint8_t)(v >> (8 * bb));
-            if (shared) put_edge(a.out_words + j.edge + 1, ob + (nb >> 3), v >> (nb & ~7) & 0xffu);
+            if (shared) put_edge(a.out_words + j.edge + 1, ob + (nb >> 3), v >> (nb & ~7) & 0xffu, a.edge_call);
         }
     };
 

@@ -41,6 +41,7 @@ struct Args {
     uint8_t *out;            // packed decoded bits
     uint32_t *out_words;     // kOutAtomic: zeroed words; kOutEdges: the boundaries' words; else null
     int64_t out_bits;        // kOutEdges: bits of the call
+    uint32_t edge_call;      // kOutEdges: number of the call
     int32_t *final_pm;       // [PB][2^V] normalized final metrics or null
     uint32_t *sp;            // survivor scratch, sp_wave_dwords per wave
     int64_t sp_wave_dwords;
