@@ -871,7 +871,6 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
     pbvd_status st = ws_survivors(ws, (size_t)(launch_waves * sp_wave_dwords * 4));
     if (st != PBVD_OK) return st;
 
-    const int64_t out_bytes = ceil_div(g.out_bits, 8);
     Output o;
     st = begin_output(ws, c.D, g.out_bits, pb_count, d_out, pbvd::tag_body_used(c.K, c.pm_bits), stream, &o);
     if (st != PBVD_OK) return st;
@@ -894,7 +893,6 @@ pbvd_status run_decode(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t 
     a.n_fold = g.n_fold;
     a.n_int_waves = g.n_int_waves;
     fold_fetch_bounds(c, g, &a.fold_i_safe, &a.fold_wide);
-    a.out_bytes = out_bytes;
     a.sp_wave_dwords = sp_wave_dwords;
     a.D = c.D;
     a.L = c.L;

@@ -72,7 +72,6 @@ __global__ void __launch_bounds__(256)
     WaveJob j;
     j.out_mode = a.out_mode;
     j.out = a.out;
-    j.out_bytes = a.out_bytes;
     j.out_words = a.out_words;
     j.out_bits = a.out_bits;
     j.edge_call = a.edge_call;
@@ -200,7 +199,6 @@ __device__ __forceinline__ void tile_body(const TileArgs &a, int64_t wave_local,
     j.store0_uniform = (tflags & kTileStore0) != 0;
     j.out_mode = kOutBytes;
     j.out = a.out;
-    j.out_bytes = 0;
     j.out_words = nullptr;
     j.out_bits = 0;
     j.edge_call = 0;

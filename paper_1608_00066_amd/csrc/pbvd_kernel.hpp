@@ -80,7 +80,6 @@ struct KernelArgs {
     int64_t n_int_waves;    // waves covering n_fold + (b_hi - b_lo) slots, 64 >> LB PBs each
     int64_t wave_begin;     // first wave (interior waves first, then edge waves)
     int64_t n_waves;        // waves in this launch
-    int64_t out_bytes;      // bytes of `out`
     int64_t out_bits;       // bits of the call
     int64_t sp_wave_dwords; // survivor dwords per wave slot
     int32_t D, L;
@@ -410,7 +409,6 @@ struct WaveJob {
     int out_mode;        // kOutDirect / kOutAtomic / kOutBytes / kOutEdges
     const uint8_t *in_end;
     uint8_t *out;
-    int64_t out_bytes;   // kOutDirect bound
     uint32_t *out_words; // kOutAtomic staging, kOutEdges words
     int64_t out_bits;    // kOutEdges: bits of the call
     uint32_t edge_call;  // kOutEdges: number of the call
@@ -667,21 +665,17 @@ __device__ __forceinline__ void decode_body(const WaveJob &j, const RowStore<Lay
 
     auto put_word = [&](int rel, int m) PBVD_INLINE_LAMBDA {
         const int64_t bitpos = j.out_bit0 + rel;
-        if (j.out_mode == kOutDirect) {
-            const int64_t byte = bitpos >> 3;
-            if (m == 32 && byte + 4 <= j.out_bytes) {
-                *reinterpret_cast<uint32_t *>(j.out + byte) = word;
-            } else {
-                for (int bb = 0; bb < ((m + 7) >> 3); ++bb)
-                    if (byte + bb < j.out_bytes) j.out[byte + bb] = (uint8_t)(word >> (8 * bb));
-            }
-        } else if (j.out_mode == kOutAtomic) {
+        if (j.out_mode == kOutAtomic) {
             const uint32_t sh = (uint32_t)(bitpos & 31);
             uint32_t *wp = j.out_words + (bitpos >> 5);
             atomicOr(wp, word << sh);
             if (sh && (word >> (32 - sh))) atomicOr(wp + 1, word >> (32 - sh));
         } else {
-            // the lane owns whole bytes: its first bit is byte aligned
+            // the lane owns whole bytes: its first bit is byte aligned (one
+            // path for kOutDirect and kOutBytes: this is inlined at every
+            // traceback step, and a path of its own for each made the stream
+            // kernel of K = 3 141 KB, more than twice the instruction cache:
+            // 64Ki blocks of 512 bits 142 -> 162 us)
             uint8_t *ob = j.out + (bitpos >> 3);
             if (m == 32 && (((uintptr_t)ob & 3u) == 0)) {
                 *reinterpret_cast<uint32_t *>(ob) = word;
