@@ -276,10 +276,11 @@ void pbvd_destroy(pbvd_plan *p);
  *     when they have the same lanes per PB, 16-bit metrics and input kind
  *     (each tile decoded with its own code);
  *   state-parallel kernel (PBVD_MAP_WAVE): the PBs of every such code of one
- *     K in ONE launch, longest first: a wave per PB where the device holds
- *     them all, else persistent waves that take PBs from work counters (one
- *     per XCD) that a fill kernel zeroes at the start of each decode; PBs
- *     of several K, up to 32 per SIMD, in one launch for all of them;
+ *     K in ONE launch, longest first: a wave per PB up to 32 per SIMD (as far
+ *     as the survivor workspace goes), else persistent waves that take PBs
+ *     from work counters (one per XCD) that a fill kernel zeroes at the start
+ *     of each decode; PBs of several K, up to 32 per SIMD, in one launch for
+ *     all of them;
  *   group mapping (PBVD_MAP_GROUP): tiles of 64 PBs, one launch per code.
  * The launches run on forked streams.  Every frame's output is identical to
  * decoding that frame alone with pbvd_decode and the same code parameters.

@@ -48,11 +48,27 @@ pbvd_status make_code_set(const pbvd_code *codes, int32_t n, CodeSet *out, int a
 
 namespace {
 
-// The longest list that one launch of every K takes, per SIMD.  PBs of K = 3,
-// 7 and 9 (D = 64) in one launch and in one per K on forked streams, us: 1357
-// PBs 16.8 and 53, 3997 18.7 and 53.8, 7958 32 and 57.6; of K = 3 and 5, 15654
-// PBs 30 and 44.
-constexpr int64_t kMixedWavesPerSimd = 32;
+// The longest list that one launch takes with a wave per PB, of one K or of
+// every K, per SIMD.  One K, a wave per PB and persistent waves that take PBs
+// from work counters (whose atomics are a chain of their own), us: K = 7 D = 16
+// 12,418 PBs 24.6 and 52, 30,727 44 and 86; D = 512 12,298 76 and 96; K = 9 D =
+// 64 12,315 88 and 103, 30,733 198 and 214.  PBs of K = 3, 7 and 9 (D = 64) in one
+// launch and in one per K on forked streams: 1357 PBs 16.8 and 53, 3997 18.7 and
+// 53.8, 7958 32 and 57.6; of K = 3 and 5, 15654 PBs 30 and 44.
+constexpr int64_t kListWavesPerSimd = 32;
+
+// The most PBs of one code that take the wave mapping where its PBs are all of a
+// batch: wave_max_pbs, but fewer of K <= 7 where blocks are short, since a tile
+// of the register kernel takes as long as its stages and a wave has a fixed cost.
+// Wave mapping and tiles, us: K = 3 52 stages (D = 16) 8.2Ki PBs 14.6 and 16.7,
+// 12.5Ki 18.7 and 16.3; K = 5 76 stages 12.4Ki 20.6 and 22.9, 16.6Ki 25.1 and
+// 21.6; K = 7 100 stages 12.4Ki 24.6 and 27.2, 16.4Ki 29.5 and 26.6, 148 stages
+// 16.4Ki 36.0 and 36.9.
+int64_t batch_wave_max_pbs(const pbvd_code &c) {
+    const int64_t most = wave_max_pbs(c.K);
+    if (c.K > 7 || getenv("PBVD_WAVE_MAX_PBS")) return most;
+    return std::min(most, 8000 + 52 * ((int64_t)c.D + 2 * (int64_t)c.L));
+}
 
 // A registered code whose mapping and lanes per PB are the library's choice.
 bool auto_mapping(const CodeSet &cs, int ci) {
@@ -475,7 +491,7 @@ struct pbvd_batch {
 namespace {
 
 // The state-parallel PBs of every K as one group (the first) where they are of
-// more than one K and few: at most kMixedWavesPerSimd waves per SIMD, with a
+// more than one K and few: at most kListWavesPerSimd waves per SIMD, with a
 // survivor slot each inside a code's share of the budget.
 void mix_waves(const CodeSet &cs, int64_t n_simd, int64_t budget, WorkList *wl) {
     FusedGroup m{};
@@ -489,7 +505,7 @@ void mix_waves(const CodeSet &cs, int64_t n_simd, int64_t budget, WorkList *wl) 
         m.n_descs += fg.n_descs;
         m.sp_wave_dwords = std::max(m.sp_wave_dwords, fg.sp_wave_dwords);
     }
-    if (n_k < 2 || m.n_descs > kMixedWavesPerSimd * n_simd || m.n_descs * m.sp_wave_dwords * 4 > budget / cs.n ||
+    if (n_k < 2 || m.n_descs > kListWavesPerSimd * n_simd || m.n_descs * m.sp_wave_dwords * 4 > budget / cs.n ||
         getenv("PBVD_PERSISTENT_WAVES"))
         return;
     for (FusedGroup &fg : wl->fused) fg = FusedGroup{};
@@ -554,22 +570,29 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
                 pbs[frames[f].code] += ceil_div(frames[f].n_bits, cs.codes[frames[f].code].D);
         // All of them on the wave mapping while the batch has few PBs: each
         // code's as a share of the most that its K decodes faster there, the
-        // shares together at most one; two where they are of several K and
-        // one launch takes them (tiles need a launch per code, and forked
-        // streams cost 20 us each): 18185 PBs of K = 3, 7 and 9, D = 64, 65 us
-        // there and 103 in tiles.
-        double share = 0;
+        // shares together at most one; where they are of several K and one
+        // launch takes them (tiles need a launch per code, one after another,
+        // and forked streams cost 20 us each) 1.5, and up to two the more of
+        // them the largest K leaves to the others.  Wave mapping and tiles, us:
+        // K = 7 and one frame of K = 3, D = 208, 24.6Ki PBs 84 and 83, 30.7Ki
+        // 105 and 86; K = 9 and one frame of K = 3, D = 512, 12.3Ki 252 and 280,
+        // 15.4Ki 325 and 283; K = 7 and 9 alike, D = 208, 20.5Ki 155 and 194;
+        // K = 3 and 7 alike, D = 64, 30.8Ki 60 and 61.
+        double share = 0, share_of[kMaxK + 1] = {};
         int64_t open = 0;
         int ks = 0;  // bit K: there are PBs of that K
         for (int ci = 0; ci < cs.n; ++ci)
             if (auto_mapping(cs, ci) && pbs[ci] > 0) {
-                const int64_t most = wave_max_pbs(cs.codes[ci].K);
-                share += most > 0 ? (double)pbs[ci] / (double)most : 2.0;
+                const int64_t most = batch_wave_max_pbs(cs.codes[ci]);
+                const double s = most > 0 ? (double)pbs[ci] / (double)most : 2.0;
+                share += s;
+                share_of[cs.codes[ci].K] += s;
                 open += pbs[ci];
                 ks |= 1 << cs.codes[ci].K;
             }
-        const bool one_launch = (ks & (ks - 1)) != 0 && open <= kMixedWavesPerSimd * device_simds(b->device);
-        const double share_max = one_launch ? 2.0 : 1.0;
+        const bool one_launch = (ks & (ks - 1)) != 0 && open <= kListWavesPerSimd * device_simds(b->device);
+        const double largest = *std::max_element(share_of, share_of + kMaxK + 1);
+        const double share_max = !one_launch ? 1.0 : 1.5 + std::min(0.5, 1.0 - largest / share);
         for (int ci = 0; ci < cs.n; ++ci) {
             if (requested_lb(cs.codes[ci]) >= 0 || cs.idx[ci] < 0) continue;
             if (share <= share_max && auto_mapping(cs, ci)) {
@@ -648,6 +671,13 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
         if (fg.mixed) {
             fused_waves[K - kMinK] = fg.n_descs;
             full += fg.n_descs * fg.sp_wave_dwords * 4;
+            continue;
+        }
+        const int64_t list_bytes = fg.n_descs * fg.sp_wave_dwords * 4;
+        if (fg.n_descs <= kListWavesPerSimd * device_simds(b->device) && list_bytes <= budget / b->cs.n &&
+            !getenv("PBVD_PERSISTENT_WAVES")) {
+            fused_waves[K - kMinK] = fg.n_descs;
+            full += list_bytes;
             continue;
         }
         int64_t res = resident_waves(K);
