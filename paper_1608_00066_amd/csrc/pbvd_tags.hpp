@@ -327,6 +327,8 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
     const uint32_t rel_end = (uint32_t)(in_left < 0x7ffffff0 ? in_left + 3 : 0x7ffffff0) & ~3u;
     // every lane's last window lies inside the input
     const bool end_ok = __ballot((int64_t)(base + (n_trips - 1) * NB + 4 * (NW + 1)) > in_left) == 0;
+    // and the one after it, which belongs to later symbols
+    const bool next_ok = __ballot((int64_t)base + (int64_t)n_trips * NB + 4 * (NW + 1) > in_left) == 0;
     const uint8_t *const win = in_dw + base;
     auto fetch = [&](uint32_t (&raw)[NW + 1], int trip) PBVD_INLINE_LAMBDA {
         const uint32_t *q = reinterpret_cast<const uint32_t *>(win + (int64_t)trip * NB);
@@ -462,7 +464,7 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
     constexpr uint64_t kBit[3] = {0xaaaaaaaaaaaaaaaaull, 0xccccccccccccccccull, 0xf0f0f0f0f0f0f0f0ull};
     auto run_trip = [&](auto modec, int trip) PBVD_INLINE_LAMBDA {
         constexpr int MODE = decltype(modec)::value;
-        static_for<0, U>([&](auto kc) PBVD_INLINE_LAMBDA {
+        auto stage = [&](auto kc) PBVD_INLINE_LAMBDA {
             constexpr int k = decltype(kc)::value, PH = k % V;
             // symbols of the stage times 16, two to a register
             T q[R];
@@ -547,6 +549,11 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
                     relabel(std::integral_constant<int, tag_lane_mask<C, LB>(PH, 2)>{}, std::integral_constant<int, 2>{});
             }
             acs_tags<C, PH, LB, MODE == kSlow>(pm, pair, force, ell);
+        };
+        static_for<0, U>([&](auto kc) PBVD_INLINE_LAMBDA {
+            constexpr int k = decltype(kc)::value;
+            // (the stages before the wave's first leave the metrics 0)
+            if (MODE != kSlow || trip * U + k >= off) stage(kc);
             if constexpr (MODE != kWarm && (k + 1) % kTagBits == 0) {
                 constexpr int q = k / kTagBits;
                 const int g = trip * CY + q;
@@ -564,12 +571,16 @@ __device__ __forceinline__ void tag_body(const WaveJob &j, uint32_t *sp_wave, in
     // Trips: slow ones while a later trip still holds a lane's start or a
     // known start is under way (their successors' symbols are fetched
     // safely), then the warm-up trips that lie before the first traced group,
-    // then the storing ones; the last trip (the last two where its window runs
-    // past the input) is a slow one again.
+    // then the storing ones.  Where the window after the last trip's runs past
+    // the input the last one is a slow one again, the last two where its own
+    // does.  A slow trip takes half as long again per stage, but the first trip
+    // as a slow one leaves out the stages before the wave's first.  (With
+    // a slow last trip in every wave, and without: 48Ki blocks of 64 bits of
+    // K = 7 54.3 and 52.3 us, 128Ki of 16 bits of K = 8 136.6 and 129.6.)
     uint32_t raw[NW + 1];
     fetch_safe(raw, 0);
     align_trip(raw, w, std::false_type{});
-    const int hot_end = n_trips - (end_ok ? 1 : 2);
+    const int hot_end = n_trips - (next_ok ? 0 : end_ok ? 1 : 2);
     int n_slow = (start_hi + U - 1) / U - 1;
     if ((force_end + U - 1) / U > n_slow) n_slow = (force_end + U - 1) / U;
     int trip = 0;
