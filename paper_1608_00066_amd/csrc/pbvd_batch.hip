@@ -57,8 +57,8 @@ namespace {
 // 53.8, 7958 32 and 57.6; of K = 3 and 5, 15654 PBs 30 and 44.
 constexpr int64_t kListWavesPerSimd = 32;
 
-// The most PBs of one code that take the wave mapping where its PBs are all of a
-// batch: wave_max_pbs, but fewer of K <= 7 where blocks are short, since a tile
+// The most PBs of one code that take the wave mapping where a batch has PBs of its
+// K only: wave_max_pbs, but fewer of K <= 7 where blocks are short, since a tile
 // of the register kernel takes as long as its stages and a wave has a fixed cost.
 // Wave mapping and tiles, us: K = 3 52 stages (D = 16) 8.2Ki PBs 14.6 and 16.7,
 // 12.5Ki 18.7 and 16.3; K = 5 76 stages 12.4Ki 20.6 and 22.9, 16.6Ki 25.1 and
@@ -572,27 +572,30 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
         // code's as a share of the most that its K decodes faster there, the
         // shares together at most one; where they are of several K and one
         // launch takes them (tiles need a launch per code, one after another,
-        // and forked streams cost 20 us each) 1.5, and up to two the more of
+        // and forked streams cost 20 us each) 1.5, and up to 2.5 the more of
         // them the largest K leaves to the others.  Wave mapping and tiles, us:
-        // K = 7 and one frame of K = 3, D = 208, 24.6Ki PBs 84 and 83, 30.7Ki
-        // 105 and 86; K = 9 and one frame of K = 3, D = 512, 12.3Ki 252 and 280,
-        // 15.4Ki 325 and 283; K = 7 and 9 alike, D = 208, 20.5Ki 155 and 194;
-        // K = 3 and 7 alike, D = 64, 30.8Ki 60 and 61.
+        // K = 7 and one frame of K = 3, D = 208, 24.6Ki PBs (shares 1.5) 84 and
+        // 83, 30.7Ki 105 and 86; K = 9 and one frame of K = 3, D = 512, 12.3Ki
+        // (1.5) 252 and 280, 15.4Ki 325 and 283; twice as many of K = 7 as of 9,
+        // D = 208, 30.7Ki (2.5) 181 and 204; K = 3 and 7 alike, D = 64, 30.8Ki
+        // (1.9) 60 and 61; six K, D = 64, 30.7Ki (2.5) 93 and 163.
         double share = 0, share_of[kMaxK + 1] = {};
         int64_t open = 0;
         int ks = 0;  // bit K: there are PBs of that K
         for (int ci = 0; ci < cs.n; ++ci)
+            if (auto_mapping(cs, ci) && pbs[ci] > 0) ks |= 1 << cs.codes[ci].K;
+        const bool one_k = (ks & (ks - 1)) == 0;
+        for (int ci = 0; ci < cs.n; ++ci)
             if (auto_mapping(cs, ci) && pbs[ci] > 0) {
-                const int64_t most = batch_wave_max_pbs(cs.codes[ci]);
+                const int64_t most = one_k ? batch_wave_max_pbs(cs.codes[ci]) : wave_max_pbs(cs.codes[ci].K);
                 const double s = most > 0 ? (double)pbs[ci] / (double)most : 2.0;
                 share += s;
                 share_of[cs.codes[ci].K] += s;
                 open += pbs[ci];
-                ks |= 1 << cs.codes[ci].K;
             }
-        const bool one_launch = (ks & (ks - 1)) != 0 && open <= kListWavesPerSimd * device_simds(b->device);
+        const bool one_launch = !one_k && open <= kListWavesPerSimd * device_simds(b->device);
         const double largest = *std::max_element(share_of, share_of + kMaxK + 1);
-        const double share_max = !one_launch ? 1.0 : 1.5 + std::min(0.5, 1.0 - largest / share);
+        const double share_max = !one_launch ? 1.0 : 1.5 + std::min(1.0, 2.0 * (1.0 - largest / share));
         for (int ci = 0; ci < cs.n; ++ci) {
             if (requested_lb(cs.codes[ci]) >= 0 || cs.idx[ci] < 0) continue;
             if (share <= share_max && auto_mapping(cs, ci)) {
