@@ -572,7 +572,7 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
         // code's as a share of the most that its K decodes faster there, the
         // shares together at most one; where they are of several K and one
         // launch takes them (tiles need a launch per code, one after another,
-        // and forked streams cost 20 us each) 1.5, and up to 2.5 the more of
+        // and forked streams cost 20 us each) 1.5, and up to 2.7 the more of
         // them the largest K leaves to the others.  Wave mapping and tiles, us:
         // K = 7 and one frame of K = 3, D = 208, 24.6Ki PBs (shares 1.5) 84 and
         // 83, 30.7Ki 105 and 86; K = 9 and one frame of K = 3, D = 512, 12.3Ki
@@ -595,7 +595,7 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
             }
         const bool one_launch = !one_k && open <= kListWavesPerSimd * device_simds(b->device);
         const double largest = *std::max_element(share_of, share_of + kMaxK + 1);
-        const double share_max = !one_launch ? 1.0 : 1.5 + std::min(1.0, 2.0 * (1.0 - largest / share));
+        const double share_max = !one_launch ? 1.0 : 1.5 + std::min(1.2, 2.2 * (1.0 - largest / share));
         for (int ci = 0; ci < cs.n; ++ci) {
             if (requested_lb(cs.codes[ci]) >= 0 || cs.idx[ci] < 0) continue;
             if (share <= share_max && auto_mapping(cs, ci)) {

@@ -88,7 +88,11 @@ int64_t device_simds(int device);
 // Waves of one SIMD share it, so a launch takes base + turn * (the waves of
 // the fullest SIMD).  More lanes per PB make a wave shorter and cost lane
 // exchanges.  Microseconds at 512 + 12 (K-1) stages, 16-bit metrics, R = 2
-// (K = 7, 8) or 3 (K = 9); other block lengths and R scale both terms alike.
+// (K = 7, 8) or 3 (K = 9); other block lengths and R are taken to scale both
+// terms alike, which holds within a tenth: the rule is off by more where the
+// usual width and another lie close, e.g. K = 7, 64Ki PBs of 148 stages, 64.8
+// us with the 1 lane it takes and 57.4 with 2; K = 7 rate 1/3, 128Ki of 596
+// stages, 448.9 with the usual 2 that it keeps and 400.5 with 1.
 // Measured at 16Ki / 32Ki / 48Ki / 64Ki / 96Ki PBs, by lanes per PB:
 //   K=7  1: 188 192 196 211 350   2: 132 140 213 217 302
 //   K=8  1: 371 388 406 468 723   2: 219 245 374 393 577   4: 155 227 320 411 591
@@ -106,9 +110,13 @@ int cheapest_lb(int K, int top, int usual, int64_t n_simd, Waves waves) {
     const Cost *const cost = kCost[K <= 7 ? 0 : K - 7];
     auto us = [&](int lb) { return cost[lb].base + cost[lb].turn * ceil_div(waves(lb), n_simd); };
     int best = usual;
-    int64_t limit = us(usual) * 20;
     for (int lb = top; lb >= 0; --lb)
-        if (lb != usual && us(lb) * 21 < limit) best = lb, limit = us(lb) * 21;
+        if (us(lb) * 21 < us(usual) * 20 && us(lb) < us(best)) best = lb;
+    // in place of one lane: of two that the model puts side by side the fewer
+    // lanes (K = 8, 206Ki PBs of frames of 100 to 300 bits, D = 16: 216 us with 1
+    // lane, 213 with 2, 233 with 4)
+    for (int lb = 1; usual == 0 && lb < best; ++lb)
+        if (us(lb) * 20 <= us(best) * 21) return lb;
     return best;
 }
 

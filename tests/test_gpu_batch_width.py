@@ -1,0 +1,22 @@
+"""The lanes per PB that a batch of many short blocks of K = 8 takes, against the
+widths it can be told to take, in time: at 206Ki PBs the library took 4 lanes, 8 %
+slower than 1 and 2.  1.06 is half-way."""
+import random
+
+import pytest
+
+from test_gpu_batch import log, pbvd, torch  # noqa: F401  (fixtures)
+from test_gpu_batch_list import _us
+
+pytestmark = pytest.mark.gpu
+
+
+def test_width_of_many_short_blocks(torch, pbvd):  # noqa: F811
+    log("batch width: K=8")
+    code = dict(K=8, gens=(0o247, 0o371), D=16, L=48)
+    rng = random.Random(21)
+    frames = [(0, rng.randint(100, 300)) for _ in range(16000)]
+    chosen = _us(torch, pbvd, [code], frames)
+    widths = {w: _us(torch, pbvd, [dict(code, lanes_per_pb=w, mapping=1)], frames) for w in (1, 2, 4)}
+    print(chosen, widths, flush=True)
+    assert chosen <= 1.06 * min(widths.values())
