@@ -232,7 +232,11 @@ pbvd_status pbvd_block_geometry(const pbvd_plan *p, int64_t n_bits, int64_t pb_f
  * survivor decisions they stored into d_dec, a device uint8 array
  * [pb_count][D+L][2^(K-1)]: row s - b*D holds the decision (1 = lower
  * branch, from S_2j+1) of every state at stage s for s in [b*D, f1); other
- * rows are zero.  d_out_bits as in pbvd_decode_ex.  Synchronizes the stream.
+ * rows are zero.  The register kernel of K >= 6 with 16-bit metrics stores, per
+ * four stages, the four decisions of every survivor: those are expanded, and
+ * the decisions of states that no survivor passes through are taken from a
+ * decode of the same PBs on the state-parallel kernel, whose bits are not
+ * kept.  d_out_bits as in pbvd_decode_ex.  Synchronizes the stream.
  * Returns PBVD_EINVAL when the range does not fit the workspace of a single
  * launch. */
 pbvd_status pbvd_debug_survivors(pbvd_plan *p, const void *d_syms, int64_t n_bits,

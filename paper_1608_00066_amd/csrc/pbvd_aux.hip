@@ -6,6 +6,7 @@
 
 #include "pbvd_aux.hpp"
 #include "pbvd_kernel.hpp"
+#include "pbvd_tag_view.hpp"
 #include "pbvd_wave_args.hpp"
 
 namespace pbvd {
@@ -104,6 +105,38 @@ __global__ void unpack_wave_survivors_kernel(SurvivorView v, uint8_t *dec) {
     }
 }
 
+// The same for the tag body, over decisions of every state already in dec: the
+// ones that the stored tags name take their place (pbvd_tag_view.hpp).  A state
+// that the known start has not reached has none (the body takes its upper
+// branch whatever the metrics).
+__global__ void unpack_tags_kernel(SurvivorView v, uint8_t *dec) {
+    const int N = 1 << (v.K - 1), V = v.K - 1, U = tag_view::trip(V);
+    const int64_t rows = (int64_t)v.D + v.L;
+    const int64_t total = v.pb_count * rows * N;
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
+         t += (int64_t)gridDim.x * blockDim.x) {
+        const int state = (int)(t % N);
+        const int64_t row = (t / N) % rows;
+        const int64_t b = v.pb_first + t / (N * rows);
+        const int64_t d0 = b * v.D;
+        const int64_t f0 = d0 - v.L < 0 ? 0 : d0 - v.L;
+        const int64_t f1 = d0 + v.D + v.L > v.T ? v.T : d0 + v.D + v.L;
+        const int64_t s = d0 + row;
+        if (s >= f1) continue;
+        if (f0 == 0 && s < V - 1 && (state & ((1 << (V - 1 - s)) - 1))) continue;
+        const WavePlace wp =
+            wave_place(b, v.pb_first, v.b_lo, v.b_hi, v.n_head, v.n_fold, v.n_int_waves, kWave >> v.lb);
+        // stages the wave runs and those it stores tags of
+        const bool edge = wp.wave >= v.n_int_waves;
+        const int64_t len = edge ? f1 - f0 : (int64_t)v.D + 2 * v.L, traced = edge ? f1 - d0 : (int64_t)v.D + v.L;
+        const int64_t end = (len + U - 1) / U * U;
+        const int64_t n_rows = end / tag_view::kStages - (end - traced) / tag_view::kStages;
+        const int got = tag_view::stored_decision(v.sp + wp.wave * v.sp_wave_dwords, n_rows, wp.slot, f1 - 1 - s,
+                                                  (uint32_t)state, V, v.lb, dec[t]);
+        if (got >= 0) dec[t] = (uint8_t)got;
+    }
+}
+
 template <int R, int KIND>
 __global__ void branch_metrics_kernel(const uint8_t *syms, int64_t n_stages, int32_t *out) {
     for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n_stages;
@@ -155,6 +188,13 @@ hipError_t unpack_survivors(const SurvivorView &v, uint8_t *dec, hipStream_t s) 
         hipLaunchKernelGGL(unpack_wave_survivors_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, v, dec);
     else
         hipLaunchKernelGGL(unpack_survivors_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, v, dec);
+    return hipGetLastError();
+}
+
+hipError_t unpack_tags(const SurvivorView &v, uint8_t *dec, hipStream_t s) {
+    const int64_t total = v.pb_count * ((int64_t)v.D + v.L) * (1 << (v.K - 1));
+    if (total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(unpack_tags_kernel, dim3(grid_for(total, 256)), dim3(256), 0, s, v, dec);
     return hipGetLastError();
 }
 

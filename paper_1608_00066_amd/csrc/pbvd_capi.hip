@@ -699,10 +699,10 @@ pbvd_status validate_call(const pbvd_plan *p, const void *d_syms, int64_t n_bits
 }
 
 // The state-parallel kernel for one call: one wave per PB, in launches of
-// as many PBs as the survivor workspace holds (at_least whatever its size).
+// as many PBs as the survivor workspace holds.
 pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int64_t n_bits,
                             int64_t pb_first, int64_t pb_count, uint8_t *d_out, int32_t *d_final_pm,
-                            hipStream_t stream, CallGeometry *geo_out, bool single_launch, int64_t at_least = 0) {
+                            hipStream_t stream, CallGeometry *geo_out, bool single_launch) {
     const pbvd_code &c = p->code;
     const int64_t D = c.D;
     const int64_t T = n_bits + (c.terminated ? c.K - 1 : 0);
@@ -717,7 +717,7 @@ pbvd_status run_decode_wave(pbvd_plan *p, Workspace &ws, const void *d_syms, int
     const int64_t slot = wave_slot_dwords(c);
     // single_launch (the debug survivor export): each wave also stores its
     // per-stage decisions, after the tags of all waves
-    const int64_t per_launch = std::max(at_least, launch_limit(p, ws, single_launch ? 2 * slot : slot));
+    const int64_t per_launch = launch_limit(p, ws, single_launch ? 2 * slot : slot);
     if (per_launch < 1)
         return fail(PBVD_EINVAL, "one PB's survivors (%lld bytes) do not fit the static scratch",
                     (long long)(slot * 4));
@@ -1049,19 +1049,31 @@ pbvd_status pbvd_debug_survivors(pbvd_plan *p, const void *d_syms, int64_t n_bit
     int lb = 0;
     st = run_decode(p, p->ws, d_syms, n_bits, pb_first, pb_count, d_out_bits, nullptr, s, &g, true, &lb);
     if (st != PBVD_OK || pb_count == 0) return st;
-    if (lb <= 3 && pbvd::tag_body_used(p->code.K, p->code.pm_bits)) {
-        // the tag body keeps four decisions of the survivors, not every
-        // state's: the state-parallel kernel's debug variant gives those, in
-        // parts whose output starts on whole words (the same bits again)
-        const int64_t slot = wave_slot_dwords(p->code);
-        const int64_t part = std::max<int64_t>(launch_limit(p, p->ws, 2 * slot) / 32, 1) * 32;
+    const bool tags = lb <= 3 && pbvd::tag_body_used(p->code.K, p->code.pm_bits);
+    if (tags) {
+        // a tag is the decisions of one survivor; the decisions of the states
+        // that no survivor passes through come from the state-parallel kernel,
+        // in parts that its workspace holds
+        struct Other {
+            Workspace ws;
+            uint32_t *bits = nullptr;
+            size_t bits_bytes = 0;
+            ~Other() {
+                free_workspace(ws);
+                if (bits) (void)hipFree(bits);
+            }
+        } other;
+        const int64_t slot = wave_slot_dwords(p->code), part = launch_limit(p, other.ws, 2 * slot);
         for (int64_t b0 = 0; b0 < pb_count; b0 += part) {
             const int64_t n = std::min(part, pb_count - b0);
-            st = run_decode_wave(p, p->ws, d_syms, n_bits, pb_first + b0, n, d_out_bits + b0 * p->code.D / 8, nullptr, s,
-                                 &g, true, n);
+            st = ensure_buffer(&other.bits, &other.bits_bytes, (size_t)(ceil_div(n * p->code.D, 32) * 4), "bits");
+            if (st != PBVD_OK) return st;
+            CallGeometry part_g{};
+            st = run_decode_wave(p, other.ws, d_syms, n_bits, pb_first + b0, n, (uint8_t *)other.bits, nullptr, s,
+                                 &part_g, true);
             if (st != PBVD_OK) return st;
             pbvd::SurvivorView v{};
-            v.sp = p->ws.sp + n * slot;
+            v.sp = other.ws.sp + n * slot;
             v.wave = 1;
             v.sp_wave_dwords = slot;
             v.T = g.T;
@@ -1075,7 +1087,6 @@ pbvd_status pbvd_debug_survivors(pbvd_plan *p, const void *d_syms, int64_t n_bit
         }
         hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-        return PBVD_OK;
     }
     pbvd::SurvivorView v{};
     // the state-parallel kernel's per-stage decisions follow its tags
@@ -1093,7 +1104,8 @@ pbvd_status pbvd_debug_survivors(pbvd_plan *p, const void *d_syms, int64_t n_bit
     v.K = p->code.K;
     v.D = p->code.D;
     v.L = p->code.L;
-    hipError_t e = pbvd::unpack_survivors(v, d_dec, s);
+    v.lb = lb;
+    hipError_t e = tags ? pbvd::unpack_tags(v, d_dec, s) : pbvd::unpack_survivors(v, d_dec, s);
     if (e != hipSuccess) return fail_hip(e, "survivor expansion launch");
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
