@@ -213,7 +213,9 @@ pbvd_status pbvd_decode_host(pbvd_plan *p, const void *h_syms, int64_t n_bits, u
  * that gives 4096 waves of 64 PBs, else pairs of lanes where the code allows
  * them when that gives 1024 waves, else the largest group the code allows --
  * or another of these widths where its waves fill the SIMDs so much better
- * that the launch is a twentieth shorter (pbvd_decode_ex_noalloc: not).
+ * that the launch is a twentieth shorter (pbvd_decode_ex_noalloc: not).  (A
+ * call that asks for final metrics of a first PB of fewer than K-1 stages takes
+ * the wave mapping where the register kernel has 16-bit metrics and K >= 6.)
  * 0 on invalid arguments. */
 int32_t pbvd_call_lanes(const pbvd_plan *p, int64_t n_bits, int64_t pb_first, int64_t pb_count);
 

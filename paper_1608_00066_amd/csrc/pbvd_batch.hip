@@ -239,7 +239,7 @@ pbvd_status build_work_list(const CodeSet &cs, const pbvd_frame *frames, int64_t
                 // shorter than 7/8 of the first: the trips until the last PB
                 // of a tile has begun take half as long again, and the slowest
                 // tile sets the end of a launch of one wave per SIMD (4096
-                // frames of 40 to 6144 bits, D = 208: 132 -> 115 us)
+                // frames of 40 to 6144 bits, D = 208: 132 -> 112 us)
                 size_t k = i + 1;
                 while (k < e && !(v[k].flags & pbvd::kLaneArgmin) && v[k].store0 == v[i].store0 &&
                        (!pair_tiles || 8 * v[k].len >= 7 * v[i].len))
@@ -462,7 +462,7 @@ struct pbvd_batch {
     TileGroup groups[kMaxCodes];
     int64_t per_launch[kMaxCodes];  // waves per launch of each code
     int64_t sp_off[kMaxCodes];      // dword offset of each code's survivor area
-    // state-parallel codes: one persistent launch per K
+    // state-parallel codes: one launch per K, or one for all
     FusedGroup fused[kMaxK - kMinK + 1];
     int64_t fused_waves[kMaxK - kMinK + 1];
     int64_t fused_sp_off[kMaxK - kMinK + 1];
@@ -476,7 +476,7 @@ struct pbvd_batch {
     size_t lanes_bytes = 0, heads_bytes = 0, descs_bytes = 0;
     uint32_t *sp = nullptr;
     size_t sp_bytes = 0;
-    // launch units (a code's tiles, or a K's persistent launch) after the
+    // launch units (a code's tiles, or a list of state-parallel PBs) after the
     // first run on these streams, forked from and joined to the caller's
     // stream with events
     hipStream_t aux[kMaxCodes] = {};
@@ -768,7 +768,7 @@ pbvd_status pbvd_batch_decode(pbvd_batch *b, const void *d_syms, uint8_t *d_out,
     if (!dg.ok) return fail(PBVD_EHIP, "cannot select device %d", b->device);
     hipStream_t s = (hipStream_t)hip_stream;
     // launch units: codes with register-kernel tiles (u >= 0: code index)
-    // and persistent launches (u < 0: -1 - (K - kMinK)); there are at most
+    // and state-parallel lists (u < 0: -1 - (K - kMinK)); there are at most
     // as many as codes
     int units[kMaxCodes], n_units = 0;
     for (int ci = 0; ci < b->cs.n; ++ci)

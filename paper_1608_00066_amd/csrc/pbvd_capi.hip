@@ -230,9 +230,11 @@ int max_lb(const pbvd_code &c) {
 
 // The wave kernel runs a PB 64 lanes wide; the register kernel is faster once
 // a call has enough PBs to fill the device with lanes.  Microseconds, wave and
-// register kernel, D = 512: K = 7 16Ki PBs 91 and 132, 24Ki 132 and 134;
-// K = 8 8Ki 92 and 135, 16Ki 172 and 155; K = 9 rate 1/3 4Ki 126 and 204, 8Ki
-// 219 and 212 (D = 64: 70 and 66).
+// register kernel, D = 512: K = 7 16Ki PBs 101 and 128, 24Ki 141 and 131 (D = 64:
+// 16Ki 32.4 and 32.9); K = 8 8Ki 102 and 133, 12Ki 143 and 138 (10Ki 39.3 and
+// 38.8); K = 9 rate 1/3 8Ki 182 and 211, 12Ki 250 and 263, 16Ki 332 and 280 (8Ki
+// 58 and 67, 12Ki 84 and 75).  K <= 5 cross at 16Ki at D = 64 or, K = 3, before
+// (16Ki 26.3 and 16.4), and at D = 512 beyond or at 13Ki.
 int64_t wave_max_pbs(int K) {
     if (const char *env = getenv("PBVD_WAVE_MAX_PBS")) return atoll(env);
     return K <= 7 ? 16384 : 8192;

@@ -16,10 +16,14 @@ namespace pbvd {
 #define PBVD_BIG_TRELLIS_WAVES_PER_EU 1
 #endif
 // Register target for 64 metric VGPRs per lane (a 256-state trellis on lane
-// pairs or 128 states on one lane, 16-bit metrics).  Three waves spill some
-// registers, all outside the stage loops; with room for two K = 9 rate 1/3 on
-// pairs is 4 to 8 % faster at D = 64 (64Ki PBs 228 -> 211 us) and 1 to 3 % slower
-// on long streams of D = 512 (256Ki PBs 2962 -> 3057 us).
+// pairs or 128 states on one lane, 16-bit metrics).  Three waves spill: K = 9 rate
+// 1/3 on pairs 88 registers in the stream kernel and 164 in the tile kernel
+// (whose two bodies share it), K = 8 on one lane 84 and 168, mostly outside the
+// stage loops; the storing loop of K = 9 moves 43 per trip of 8 stages (some
+// 2,250 vector instructions), that of K = 8 3 to 6 per 28 stages, the stream
+// kernel's warm-up loops none.  With room for two waves K = 9 rate 1/3 on pairs is
+// 4 to 8 % faster at D = 64 (64Ki PBs 228 -> 211 us) and 1 to 3 % slower on long
+// streams of D = 512 (256Ki PBs 2962 -> 3057 us).
 #ifndef PBVD_MID_TRELLIS_WAVES_PER_EU
 #define PBVD_MID_TRELLIS_WAVES_PER_EU 3
 #endif
@@ -80,10 +84,12 @@ __global__ void __launch_bounds__(256)
     if (wave == 0 && a.n_fold > 0) {
         // ---- wave 0 with folded edge PBs: every lane has its own geometry
         //      (Sec. III-A, clipped to the stream), decoded like a batch tile.
-        //      A lane shorter than the wave runs on past its own end, so its
-        //      metrics at the wave's end are not its final metrics: the host
-        //      folds no PB that starts its traceback from the best state and
-        //      folds nothing when final metrics are asked for. ----
+        //      In the row body all lanes start together and a lane shorter than
+        //      the wave runs on past its own end, so its metrics at the wave's
+        //      end are not its final metrics: therefore the host folds no PB
+        //      that starts its traceback from the best state and folds nothing
+        //      when final metrics are asked for.  (In the tag body all lanes
+        //      end together.) ----
         int64_t b;
         bool active = true;
         if (pl < a.n_fold) {

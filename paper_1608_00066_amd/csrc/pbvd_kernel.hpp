@@ -244,10 +244,11 @@ constexpr int kBufferFlags = 0x00020000;  // raw 32-bit data format (gfx9 family
 // again (measured: 2.47 -> 1.93 GB fetched per 2^27-bit K=7 launch).
 constexpr int kRowPolicy = 2;  // nt
 
-// A lane moves its NDW dwords of a row of 64 lanes.  Stores move at most 8 bytes per lane: the vector memory unit reads the data registers
-// of a wider store over several cycles after it issues, and an instruction
-// that overwrites them too soon (which the compiler does not always prevent)
-// changes what the last lanes store.  8-byte stores have no such window.
+// A lane moves its NDW dwords of a row of 64 lanes.  Stores move at most 8 bytes
+// per lane: the vector memory unit reads the data registers of a wider store
+// over several cycles after it issues, and an instruction that overwrites them
+// too soon (which the compiler does not always prevent) changes what the last
+// lanes store.  8-byte stores have no such window.
 template <int NDW>
 struct RowStore {
     __amdgpu_buffer_rsrc_t rsrc;

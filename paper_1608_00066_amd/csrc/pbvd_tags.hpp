@@ -45,8 +45,9 @@
 // a wave on every SIMD the traceback reads its rows all at once, 270 cycles per
 // stage or 4.6 TB/s.  2^27 bits move 3.1 GB of rows and symbols in 0.71 ms,
 // 4.3 TB/s where a large copy reaches 4.8.  Per decode, with decisions taken
-// stage by stage and with tags: 2^27 bits of K = 7 819 -> 712 us, 2^25 bits of
-// K = 9 rate 1/3 993 -> 831 us, 12 Mbit of K = 7 in 24,001 PBs 163 -> 142 us.
+// stage by stage and with tags: 2^27 bits of K = 7 819 -> 707 us, 2^25 bits of
+// K = 9 rate 1/3 993 -> 829 us, 12 Mbit of K = 7 in 24,001 PBs 163 -> 128 us (of
+// which 12 by the output without staging).
 #pragma once
 
 #include "pbvd_kernel.hpp"
@@ -165,11 +166,11 @@ __device__ __forceinline__ int select_lanes(int a, int b, uint64_t pattern) {
 }
 
 // ---------------------------------------------------------------------------
-// Lanes per PB.  With 2^LB lanes per PB (LB = 1 or 2) the registers of a PB
+// Lanes per PB.  With 2^LB lanes per PB (LB = 1, 2 or 3) the registers of a PB
 // are spread over a group of consecutive lanes: lane l of the group holds the
 // states whose register index has l in its top LB bits.  Stages whose
-// butterfly pairs registers of different lanes read the partner's metrics
-// with a DPP quad permute; every lane keeps its own half of each pair.
+// butterfly pairs registers of different lanes swap candidates with DPP (quad
+// permutes, row shifts across quads); every lane keeps its own half of each pair.
 // ---------------------------------------------------------------------------
 // quad-permute control: flip lane bit 0 / 1
 template <int B> __host__ __device__ constexpr int quad_flip() { return B == 0 ? quad_sel(1, 0, 3, 2) : quad_sel(2, 3, 0, 1); }
