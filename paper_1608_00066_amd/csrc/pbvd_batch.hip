@@ -665,55 +665,67 @@ pbvd_status pbvd_batch_set_frames(pbvd_batch *b, const pbvd_frame *frames, int64
     // PB count (fewer waves when the budget is short).
     const int64_t budget = workspace_budget_bytes();
     mix_waves(b->cs, device_simds(b->device), budget, &wl);
-    int64_t fused_waves[kMaxK - kMinK + 1] = {};
-    int64_t full = 0;
-    for (int ci = 0; ci < b->cs.n; ++ci) full += wl.groups[ci].n_tiles * wl.groups[ci].sp_wave_dwords * 4;
-    for (int K = kMinK; K <= kMaxK; ++K) {
-        const FusedGroup &fg = wl.fused[K - kMinK];
-        if (fg.n_descs == 0) continue;
-        if (fg.mixed) {
-            fused_waves[K - kMinK] = fg.n_descs;
-            full += fg.n_descs * fg.sp_wave_dwords * 4;
-            continue;
+    int64_t fused_waves[kMaxK - kMinK + 1], fused_sp_off[kMaxK - kMinK + 1];
+    int64_t per_launch[kMaxCodes], sp_off[kMaxCodes];
+    int64_t full = 0, total = 0;  // bytes of everything at once, dwords of the areas
+    bool any_list = false;
+    auto size_areas = [&](bool lists) -> pbvd_status {
+        full = total = 0;
+        any_list = false;
+        for (int ci = 0; ci < b->cs.n; ++ci) full += wl.groups[ci].n_tiles * wl.groups[ci].sp_wave_dwords * 4;
+        for (int K = kMinK; K <= kMaxK; ++K) {
+            const FusedGroup &fg = wl.fused[K - kMinK];
+            int64_t &w = fused_waves[K - kMinK];
+            w = 0;
+            if (fg.n_descs == 0) continue;
+            const bool list = lists && fg.n_descs <= kListWavesPerSimd * device_simds(b->device) &&
+                              !getenv("PBVD_PERSISTENT_WAVES");
+            if (fg.mixed || list) {
+                w = fg.n_descs;
+                any_list = any_list || !fg.mixed;
+            } else {
+                int64_t res = resident_waves(K);
+                if (res <= 0) return fail(PBVD_EHIP, "occupancy query of the K=%d persistent kernel failed", K);
+                // PBVD_PERSISTENT_WAVES caps the waves (tests: many PBs per wave)
+                if (const char *env = getenv("PBVD_PERSISTENT_WAVES"))
+                    if (atoll(env) > 0) res = std::min<int64_t>(res, atoll(env));
+                w = std::min(fg.n_descs, res);
+            }
+            full += w * fg.sp_wave_dwords * 4;
         }
-        const int64_t list_bytes = fg.n_descs * fg.sp_wave_dwords * 4;
-        if (fg.n_descs <= kListWavesPerSimd * device_simds(b->device) && list_bytes <= budget / b->cs.n &&
-            !getenv("PBVD_PERSISTENT_WAVES")) {
-            fused_waves[K - kMinK] = fg.n_descs;
-            full += list_bytes;
-            continue;
+        for (int ci = 0; ci < b->cs.n; ++ci) {
+            const TileGroup &g = wl.groups[ci];
+            int64_t n = g.n_tiles;
+            if (full > budget) n = std::min(n, std::max<int64_t>(1, budget / b->cs.n / (g.sp_wave_dwords * 4)));
+            per_launch[ci] = std::max<int64_t>(1, n);
+            sp_off[ci] = total;
+            total += g.n_tiles > 0 ? per_launch[ci] * g.sp_wave_dwords : 0;
         }
-        int64_t res = resident_waves(K);
-        if (res <= 0) return fail(PBVD_EHIP, "occupancy query of the K=%d persistent kernel failed", K);
-        // PBVD_PERSISTENT_WAVES caps the waves (tests: many PBs per wave)
-        if (const char *env = getenv("PBVD_PERSISTENT_WAVES"))
-            if (atoll(env) > 0) res = std::min<int64_t>(res, atoll(env));
-        fused_waves[K - kMinK] = std::min(fg.n_descs, res);
-        full += fused_waves[K - kMinK] * fg.sp_wave_dwords * 4;
-    }
-    int64_t per_launch[kMaxCodes], sp_off[kMaxCodes], total = 0;
-    for (int ci = 0; ci < b->cs.n; ++ci) {
-        const TileGroup &g = wl.groups[ci];
-        int64_t n = g.n_tiles;
-        if (full > budget) n = std::min(n, std::max<int64_t>(1, budget / b->cs.n / (g.sp_wave_dwords * 4)));
-        per_launch[ci] = std::max<int64_t>(1, n);
-        sp_off[ci] = total;
-        total += g.n_tiles > 0 ? per_launch[ci] * g.sp_wave_dwords : 0;
-    }
-    int64_t fused_sp_off[kMaxK - kMinK + 1] = {};
-    for (int K = kMinK; K <= kMaxK; ++K) {
-        const FusedGroup &fg = wl.fused[K - kMinK];
-        int64_t &w = fused_waves[K - kMinK];
-        if (fg.n_descs == 0) continue;
-        if (full > budget && !fg.mixed)
-            w = std::min(w, std::max<int64_t>(1, budget / b->cs.n / (fg.sp_wave_dwords * 4)));
-        fused_sp_off[K - kMinK] = total;
-        total += w * fg.sp_wave_dwords;
-    }
+        for (int K = kMinK; K <= kMaxK; ++K) {
+            const FusedGroup &fg = wl.fused[K - kMinK];
+            int64_t &w = fused_waves[K - kMinK];
+            fused_sp_off[K - kMinK] = total;
+            if (fg.n_descs == 0) continue;
+            if (full > budget && !fg.mixed)
+                w = std::min(w, std::max<int64_t>(1, budget / b->cs.n / (fg.sp_wave_dwords * 4)));
+            total += w * fg.sp_wave_dwords;
+        }
+        return PBVD_OK;
+    };
+    // a wave per PB where the areas of all fit the budget and can be allocated
+    st = size_areas(true);
+    if (st == PBVD_OK && any_list && full > budget) st = size_areas(false);
+    if (st != PBVD_OK) return st;
     st = ensure_buffer(&b->counters, &b->counters_bytes, (size_t)(kMaxK - kMinK + 1) * kCounterDwords * 4,
                        "work counters");
     if (st != PBVD_OK) return st;
     st = ensure_buffer(&b->sp, &b->sp_bytes, (size_t)std::max<int64_t>(total, 64) * 4, "survivors");
+    if (st == PBVD_ENOMEM && any_list) {
+        st = size_areas(false);
+        if (st == PBVD_OK)
+            st = ensure_buffer(&b->sp, &b->sp_bytes, (size_t)std::max<int64_t>(total, 64) * 4, "survivors");
+        if (st == PBVD_OK) g_last_error[0] = 0;
+    }
     if (st == PBVD_OK && fault_injected("batch_alloc"))
         st = fail(PBVD_ENOMEM, "injected allocation failure after the survivor area");
     if (st != PBVD_OK) return st;
